@@ -466,7 +466,8 @@ int trimmoe_consistency_labels(int32_t n_rows, const int32_t* pred, const int32_
  * each epoch starts from.  h [n_rows, d] in `dtype` (bf16: d a multiple of
  * 64).  Sums run in a fixed order in fp64: repeated runs give identical
  * weights.  Needs a 256-byte aligned workspace of
- * trimmoe_train_exit_head_workspace_size(n_rows) bytes.
+ * trimmoe_train_exit_head_workspace_size(n_rows) bytes (room for partial
+ * column sums, with which the rows are read once per step).
  */
 int trimmoe_train_exit_head_workspace_size(int32_t n_rows, size_t* bytes);
 int trimmoe_train_exit_head(int32_t dtype, int32_t d_model, int32_t n_rows, const void* h,

@@ -83,6 +83,10 @@ inline int exit_tile_rows(bool bf16, int T) {
 }
 // fp32 GEMM tile
 constexpr int kF32Tile = 16;
+// exit-head training: the one-pass descent step takes heads of up to
+// kTrainMaxCols columns and at most kTrainBlocks blocks of partial sums
+constexpr int kTrainMaxCols = 4096;
+constexpr int kTrainBlocks = 256;
 // per-layer trace counters (row stride of trimmoe_trace.counters)
 constexpr int kCounters = 16;
 // look-ahead: later layers a decision looks at, and first-level branches
@@ -250,6 +254,13 @@ hipError_t launch_set_int(int32_t* p, int v, hipStream_t st);
 hipError_t launch_bce_step(bool bf16, const void* H, const uint8_t* y, int n_rows, int d,
                            float lr, float* w, float* c, float* r, double* row_loss,
                            float* loss_out, hipStream_t st);
+// the same step with the rows read once (d <= kTrainMaxCols): part holds nb
+// rows of bce_slots partial column sums (the columns padded to what the
+// kernel's lanes cover), part_rl nb partial (residual, loss) sums
+int bce_slots(bool bf16, const void* H, int d, int* vec);
+hipError_t launch_bce_rows_step(bool bf16, const void* H, const uint8_t* y, int n_rows, int d,
+                                float lr, float* w, float* c, double* part, double2* part_rl,
+                                int nb, float* loss_out, hipStream_t st);
 hipError_t launch_window_stats(const WindowArgs& w, hipStream_t st);
 
 // launchers (gemm.hip)

@@ -66,6 +66,42 @@ def test_training_matches_oracle(dtype):
     assert torch.equal(w, w2) and torch.equal(c, c2)
 
 
+@pytest.mark.parametrize("dtype,Q,d", [
+    (torch.bfloat16, 1, 64), (torch.bfloat16, 5, 576), (torch.bfloat16, 1029, 4096),
+    (torch.bfloat16, 37, 4160),                        # past the one-pass step's columns
+    (torch.float32, 3, 1), (torch.float32, 66, 63), (torch.float32, 1100, 260),
+    (torch.float32, 9, 4096), (torch.float32, 9, 4097),
+])
+def test_training_steps_at_the_edges(dtype, Q, d):
+    """Row and column remainders of the descent step, and the two-kernel step
+    of a workspace that holds no partials.  Logits are fp32 sums of d terms of
+    about 0.1: their error, d * 2^-24 * |sum of terms| / d, stays under 1e-5."""
+    log(f"[exit-head] edges {dtype} Q={Q} d={d}")
+    epochs, lr = 3, 0.5
+    H, Hn = _mat(31, 5, (Q, d), 1.0, dtype)
+    y = (np.arange(Q) % 3 == 0).astype(np.uint8)
+    Hd, yd = H.to(DEV), torch.from_numpy(y).to(DEV)
+    ww, cw, lw = X.train_exit_head(Hn, y, epochs, lr)
+    lib = abi.lib()
+    small = ((Q * 4 + 255) // 256 + (Q * 8 + 255) // 256) * 256
+    for nbytes in (None, small):
+        w = torch.zeros(d, dtype=torch.float32, device=DEV)
+        c = torch.zeros(1, dtype=torch.float32, device=DEV)
+        loss = torch.zeros(epochs, dtype=torch.float32, device=DEV)
+        if nbytes is None:
+            abi.trimmoe_train_exit_head(Hd, yd, epochs, lr, w, c, loss)
+        else:
+            ws = abi._aligned_ws(nbytes, Hd.device)
+            rc = lib.trimmoe_train_exit_head(abi._dtype_code(Hd), d, Q, abi._ptr(Hd), abi._ptr(yd),
+                                             epochs, lr, abi._ptr(w), abi._ptr(c), abi._ptr(loss),
+                                             abi._ptr(ws), nbytes, abi._stream_handle(None))
+            assert rc == abi.TRIMMOE_OK
+        torch.cuda.synchronize()
+        assert np.allclose(w.cpu().numpy(), ww, rtol=1e-4, atol=1e-5)
+        assert c.item() == pytest.approx(cw, rel=1e-4, abs=1e-5)
+        assert np.allclose(loss.cpu().numpy(), lw, rtol=1e-5, atol=1e-5)
+
+
 def test_trained_heads_drive_a_sigmoid_stack():
     # no planted exit direction and wider experts, so that some tokens'
     # predictions still change after layer 0 (labels of both kinds)
