@@ -141,7 +141,7 @@ size_t down_slice_rows_max(const trimmoe_model* m, int T) {
 size_t exit_partials_max(const trimmoe_model* m, int T) {
   const bool bf16 = m->dtype == TRIMMOE_BF16;
   size_t n = (size_t)T * cdiv(m->vocab_exit, exit_tile_rows(bf16, T));
-  const int Ts = std::min(T, kExitSmallTokens);
+  const int Ts = std::min(T, kSkinnyTokens);
   return std::max(n, (size_t)Ts * cdiv(m->vocab_exit, exit_tile_rows(bf16, Ts)));
 }
 
@@ -251,6 +251,8 @@ void fill_params(LayerParams& P, const trimmoe_model* m, int l, const trimmoe_po
     P.sk_flag = nullptr;
     P.sk_part = nullptr;
   }
+  // the weight-streaming down GEMM sums its K split in the block
+  if (T <= kSkinnyTokens) P.down_splits = 1;
   for (int j = 0; j < kMaxLookahead; ++j) {
     const bool later = j + 1 < P.horizon;  // layer l + j + 1 is looked at
     const trimmoe_layer* Lj = later ? &m->layers[l + j + 1] : nullptr;
@@ -322,6 +324,7 @@ int run_layer(const trimmoe_model* m, int l, const trimmoe_policy* pol, const tr
       ncu <= 0)
     return TRIMMOE_ERR_HIP;
   P.n_cu = ncu;
+  P.n_vtiles = exit_vtiles(m->dtype == TRIMMOE_BF16, s->n_tokens, m->vocab_exit, ncu);
   P.clk = clock_record_for(dev);
   const bool bf16 = m->dtype == TRIMMOE_BF16;
   const bool last = l == m->n_layers - 1;
@@ -596,6 +599,7 @@ int trimmoe_head_argmax(int32_t dtype, int32_t vocab, int32_t d_model, int32_t n
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return TRIMMOE_ERR_HIP;
+  nvt = exit_vtiles(bf16, n_rows, vocab, ncu);
   hipStream_t st = static_cast<hipStream_t>(stream);
   int32_t* n_dev = static_cast<int32_t*>(workspace);
   float2* partials = reinterpret_cast<float2*>(static_cast<char*>(workspace) + 256);

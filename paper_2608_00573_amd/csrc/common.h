@@ -70,16 +70,31 @@ inline bool big_exit(bool bf16, int T, int V, int d) {
 constexpr int kWideTokens = 4096;
 constexpr int kGemmBN = 128;
 constexpr int kGemmBK = 64;
-// vocabulary rows of one exit-head tile (bf16 MFMA path / fp32 path); bf16
-// batches of kExitSmallTokens or fewer use kExitTileBF16Small-row tiles, so
-// that a decode-sized batch still spreads W_exit over every CU
+// bf16 batches of up to this many tokens run the weight-streaming kernels
+// (skinny.hip) for every GEMM
+constexpr int kSkinnyTokens = 64;
+// vocabulary rows per exit partial (bf16 MFMA tiles / fp32 path).  The
+// weight-streaming exit head writes one partial per block; its workspace is
+// sized for blocks of at least kExitTileBF16Small rows
 constexpr int kExitTileBF16 = 256;
 constexpr int kExitTileBF16Small = 128;
-constexpr int kExitSmallTokens = 64;
 constexpr int kExitTileF32 = 16;
 
+// Operand order of the activations those kernels read: a tile of n <= 16 rows
+// is kept as [k-step of 32][4 groups of 8][n rows][8 elements], so that the
+// operand of a k-step is one contiguous run; element offset of (k-step, group,
+// row) within the tile
+__host__ __device__ inline int frag_order(int kstep, int group, int row, int n) {
+  return ((kstep * 4 + group) * n + row) * 8;
+}
+
 inline int exit_tile_rows(bool bf16, int T) {
-  return bf16 ? (T <= kExitSmallTokens ? kExitTileBF16Small : kExitTileBF16) : kExitTileF32;
+  return bf16 ? (T <= kSkinnyTokens ? kExitTileBF16Small : kExitTileBF16) : kExitTileF32;
+}
+// exit partials per token of a launch on n_cu compute units
+inline int exit_vtiles(bool bf16, int T, int V, int n_cu) {
+  const int rows = exit_tile_rows(bf16, T), n = (V + rows - 1) / rows;
+  return bf16 && T <= kSkinnyTokens && n > n_cu ? n_cu : n;
 }
 // fp32 GEMM tile
 constexpr int kF32Tile = 16;
@@ -204,7 +219,8 @@ struct LayerParams {
   int down_splits;     // K splits of the routed down GEMM (bf16 path)
   void* act_s;         // [T, Fs]
   float* y_s;          // [T, d]
-  void* hx;            // [T, d]    updated rows of executed tokens (exit input)
+  void* hx;            // [T, d]    updated rows of executed tokens (exit input;
+                       // in operand order for the weight-streaming exit head)
   float2* partials;    // [T, n_vtiles] (max, sum exp) per vocabulary tile
   int n_vtiles;
   int max_tiles;

@@ -1159,6 +1159,12 @@ __global__ __launch_bounds__(256) void k_combine(LayerParams p) {
     ST* hr = h + (size_t)t * p.d + c;
     ST* xr = static_cast<ST*>(p.hx) + (size_t)j * p.d + c;
     if constexpr (sizeof(ST) == 2) {
+      // the weight-streaming exit head reads hx in operand order
+      if (p.T <= kSkinnyTokens) {
+        const int b = j & ~15;
+        xr = static_cast<ST*>(p.hx) + (size_t)b * p.d +
+             frag_order(c >> 5, (c >> 3) & 3, j - b, min(16, n_x - b));
+      }
       union {
         uint4 v;
         ST e[8];

@@ -28,11 +28,10 @@
 // fp32 path: plain FMA kernels for fp32 models.
 #include <math.h>
 
-#include "common.h"
+#include "gemm.h"
 
 namespace trimmoe {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int BK = kGemmBK;  // 64 bf16 = one 128-byte row segment
@@ -138,11 +137,6 @@ template <int N, class T>
 __device__ __forceinline__ void slice_barrier(Frags<T>& f) {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
   frags_after(f);
-}
-
-// barrier for plain LDS traffic that leaves the DMA stream in flight
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // Ring depth: three stages (two slices in flight ahead of the one being
@@ -401,88 +395,11 @@ __device__ __forceinline__ void dma_gemm_stream(char* lds, int ntiles, int nk, c
   }
 }
 
-// ----------------------------------------------- activation helpers --
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ float swap_pair(float v) {
-  // lane l reads lane l ^ 1 (quad_perm [1, 0, 3, 2])
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xb1, 0xf,
-                                                             0xf, false));
-}
-
-// The values of lanes l and l ^ 16 (lanes_xor16) or l and l ^ 32
-// (lanes_xor32) in every lane, by gfx950's permlane swaps instead of an LDS
-// exchange: (a, b) is (own, other) in lanes 0..15 (xor16: every even row of
-// 16 lanes) or 0..31 (xor32) and (other, own) in the rest, so a commutative
-// reduction of a and b gives every lane the pair's result.  The two results
-// are copied out of the returned pair before the bit casts: a bit cast of
-// the subscripted second element read the first one.
-struct LanePair {
-  float a, b;
-};
-__device__ __forceinline__ LanePair lanes_xor16(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned r0 = r[0], r1 = r[1];
-  return {__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)};
-}
-__device__ __forceinline__ LanePair lanes_xor32(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const unsigned r0 = r[0], r1 = r[1];
-  return {__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1)};
-}
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  const bf16x2_t v = {(__bf16)lo, (__bf16)hi};
-  return __builtin_bit_cast(uint32_t, v);
-}
-
-// silu(g) u = g u / (1 + e^-g) with the hardware exp2 and reciprocal (about
-// 1 ulp each in fp32; callers round the result to bf16)
-__device__ __forceinline__ float silu_mul(float g, float u) {
-  return g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-g * 1.4426950408889634f)) * u;
-}
-
 // ------------------------------------------------------ grouped FFN GEMMs --
 // Row tiles come from the device tile list (expert, first row, end row) of
 // the expert-sorted rows, or (dense mode, shared expert) cover the first
 // *dense_rows rows.  A rows are gathered through x_idx (the token whose h
 // row feeds each sorted row) when it is set.
-// Engine-clock record (measurement only): with a record set, a block adds the
-// core clock cycles (s_memtime) and the 100 MHz constant-clock ticks
-// (s_memrealtime) between its start and the end of its work to rec[0] and
-// rec[1]; their ratio is the mean engine clock under the kernel.  The start
-// values are subtracted at once (modulo 2^64) and the end values added at
-// the end, so nothing is held in registers in between.
-__device__ __forceinline__ void clock_mark(unsigned long long* rec, bool start) {
-  if (rec && threadIdx.x == 0) {
-    const unsigned long long t = __builtin_amdgcn_s_memtime();
-    const unsigned long long r = __builtin_amdgcn_s_memrealtime();
-    atomicAdd(rec, start ? 0ull - t : t);
-    atomicAdd(rec + 1, start ? 0ull - r : r);
-  }
-}
-
-struct FfnArgs {
-  const bf16_t* X;        // [rows, K], or h [T, K] when x_idx is set
-  const int* x_idx;       // row -> source row of X (gather), or NULL
-  const bf16_t* W0;       // expert 0 of [E, N, K] (up, or down)
-  const bf16_t* W1;       // gate, same layout, or NULL
-  size_t w_stride;        // elements between experts
-  int K, N;
-  const int4* tiles;      // grouped mode
-  const int* n_tiles;     // grouped mode: live tiles (device)
-  const int* dense_rows;  // dense mode: live rows (device), else NULL
-  void* out;              // up: bf16 [rows, N]; down: f32 [split][rows_cap, N]
-  size_t split_stride;    // elements between split slices of `out`
-  int n_split;            // K splits (down GEMM); 1 otherwise
-  int act;                // up: TRIMMOE_ACT_*
-  int* sk_flag;           // large-group down GEMM: per-tile piece words (see SkPlan), or NULL
-  float* sk_part;         // ... and the compact partials of pieces 1.. of cut tiles
-  unsigned long long* clk;  // engine-clock record of this class (see clock_mark), or NULL
-};
-
 template <class T, bool UP>
 struct FfnSrc {
   struct Desc {
@@ -616,8 +533,6 @@ constexpr int B0 = 2 * AB;               // first B stage, after the two A stage
 constexpr int LDS = 2 * AB + BS * BB;    // 160 KB
 constexpr int RPP = THREADS / 8;         // rows per fetch pass (8 threads per 128-byte row)
 }  // namespace big
-
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // a wavefront's fragments of one 32-wide k-step: A rows +16 i, B columns +16 j
 struct FragA {
@@ -1184,16 +1099,6 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
 // Epilogue: for every token column, max and sum exp over the tile's
 // vocabulary rows (bias added), written as one partial per vocabulary tile
 // as (max z * log2 e, sum exp(z - max z)).
-struct ExitArgs {
-  const bf16_t* W;    // [V, K]
-  const bf16_t* H;    // [n_x, K]
-  const float* bias;  // [V] or NULL
-  const int* n_exec;  // device
-  int V, K, n_vtiles;
-  float2* partials;   // [n_x, n_vtiles]
-  unsigned long long* clk;  // engine-clock record (see clock_mark), or NULL
-};
-
 using ExitTile = Tile<kExitTileBF16, 128, 1, 4, 2>;
 // 256 tokens per tile for large batches: 64 x 128 wavefront tiles read 3/4 of
 // the LDS bytes per MFMA of the 64 x 64 ones and the DMA writes 2/3, which
@@ -1202,10 +1107,6 @@ using ExitTile = Tile<kExitTileBF16, 128, 1, 4, 2>;
 // ring (the 128-token tile keeps three stages, and its finer token tiles
 // balance the persistent grid better at small n_x)
 using ExitWide = Tile<kExitTileBF16, 256, 1, 4, 2>;
-// decode-sized batches (kExitSmallTokens or fewer): 32 token columns, 128
-// vocabulary rows, so the tiles cover the CUs and the MFMA work is not 4x
-// padding; W_exit streaming (HBM) bounds it
-using ExitSmall = Tile<kExitTileBF16Small, 32, 1, 4, 1>;
 
 template <class T, bool ARGMAX = false>
 struct ExitSrc {
@@ -1621,8 +1522,6 @@ __global__ __launch_bounds__(256) void k_exit_f32(const float* W, const float* H
 }
 
 // ------------------------------------------------------------- launchers --
-static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
 // Tile shapes of the expert GEMMs (BM rows of an expert group x BN outputs).
 // Three-stage rings: the expert weights stream from HBM, and two slices in
 // flight measured faster than 256-row two-stage tiles even for large groups.
@@ -1696,6 +1595,7 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
               p.clk ? p.clk + 2 * (shared ? TRIMMOE_CLASS_SHARED
                                           : up ? TRIMMOE_CLASS_UP : TRIMMOE_CLASS_DOWN)
                     : nullptr};
+    if (p.T <= kSkinnyTokens) return launch_ffn_skinny(a, up, dual, p.n_cu, st);
     if (big) {
       const int big_mt = shared ? cdiv(p.T, kBigBM) : cdiv(p.T * p.k, kBigBM) + p.E;
       if (up && dual)
@@ -1744,13 +1644,11 @@ hipError_t launch_exit_head(const LayerParams& p, bool bf16, hipStream_t st) {
     ExitArgs a{static_cast<const bf16_t*>(p.w_exit), static_cast<const bf16_t*>(p.hx), p.b_exit,
                &p.counts[kCntExec], p.V, p.d, p.n_vtiles, p.partials,
                p.clk ? p.clk + 2 * TRIMMOE_CLASS_EXIT : nullptr};
+    if (p.T <= kSkinnyTokens) return launch_exit_skinny(a, false, st);
     // persistent: at most one block per CU, none beyond the tile bound
     if (big_exit(true, p.T, p.V, p.d)) {
       const dim3 grid(min(p.n_vtiles * cdiv(p.T, big::BN), p.n_cu));
       hipLaunchKernelGGL(k_exit_big, grid, dim3(big::THREADS), 0, st, a);
-    } else if (p.T <= kExitSmallTokens) {
-      const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitSmall::BN), p.n_cu));
-      hipLaunchKernelGGL(k_exit_mma<ExitSmall>, grid, dim3(ExitSmall::THREADS), 0, st, a);
     } else if (p.T >= kWideTokens) {
       const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitWide::BN), p.n_cu));
       hipLaunchKernelGGL(k_exit_mma<ExitWide>, grid, dim3(ExitWide::THREADS), 0, st, a);
@@ -1774,10 +1672,8 @@ hipError_t launch_head_argmax_partials(bool bf16, const void* W, const float* bi
   if (bf16) {
     ExitArgs a{static_cast<const bf16_t*>(W), static_cast<const bf16_t*>(H), bias, n_rows_dev, V,
                K, n_vtiles, partials};
-    if (n_rows <= kExitSmallTokens) {
-      const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitSmall::BN), n_cu));
-      hipLaunchKernelGGL((k_exit_mma<ExitSmall, true>), grid, dim3(ExitSmall::THREADS), 0, st, a);
-    } else if (n_rows >= kWideTokens) {
+    if (n_rows <= kSkinnyTokens) return launch_exit_skinny(a, true, st);
+    if (n_rows >= kWideTokens) {
       const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitWide::BN), n_cu));
       hipLaunchKernelGGL((k_exit_mma<ExitWide, true>), grid, dim3(ExitWide::THREADS), 0, st, a);
     } else {

@@ -41,15 +41,24 @@ pytestmark = pytest.mark.skipif(not shutil.which(HIPCC) and not os.path.exists(H
                                 reason="hipcc not available")
 
 
-@pytest.fixture(scope="module")
-def asm(tmp_path_factory):
-    out = tmp_path_factory.mktemp("gemm_asm") / "gemm.s"
+def _compile(tmp_path_factory, src):
+    out = tmp_path_factory.mktemp("gemm_asm") / (src + ".s")
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature",
            "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           "--cuda-device-only", "-S", os.path.join(CSRC, "gemm.hip"), "-o", str(out)]
+           "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", str(out)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     return out.read_text()
+
+
+@pytest.fixture(scope="module")
+def asm(tmp_path_factory):
+    return _compile(tmp_path_factory, "gemm.hip")
+
+
+@pytest.fixture(scope="module")
+def skinny_asm(tmp_path_factory):
+    return _compile(tmp_path_factory, "skinny.hip")
 
 
 def _function(text, name):
@@ -236,6 +245,51 @@ def test_first_core_hot_loops_do_not_spill(asm):
         for s, e in _loops_with_mfma(body):
             spills = [b for b in body[s:e] if b.startswith("scratch_")]
             assert not spills, (name, spills[:4])
+
+
+def _mfma_lds_hazards(body):
+    """LDS writes of a VGPR that an MFMA wrote fewer than WAIT_STATES wait
+    states earlier on some path (the stores are inline asm, so the compiler
+    inserts no wait states before them)."""
+    succ = _cfg(body)
+    found = []
+    for i, ins in enumerate(body):
+        if not ins.startswith("v_mfma"):
+            continue
+        dst = _vgprs(ins.split(",")[0])
+        stack = [(j, WAIT_STATES) for j in succ(i)]
+        seen = set()
+        while stack:
+            j, left = stack.pop()
+            if left <= 0 or (j, left) in seen:
+                continue
+            seen.add((j, left))
+            cur = body[j]
+            if cur.startswith("ds_write") and _vgprs(cur) & dst:
+                found.append((i, ins, j, cur))
+                continue
+            m = re.match(r"s_nop\s+(\d+)", cur)
+            cost = 0 if cur.endswith(":") else int(m.group(1)) + 1 if m else 1
+            for k in succ(j):
+                stack.append((k, left - cost))
+    return found
+
+
+def test_weight_streaming_kernels(skinny_asm):
+    """Their fragment reads land before use, the stores of K parts wait for
+    the MFMAs, weights stay off the scratch memory, and every DMA takes its
+    buffer from scalar registers (a resource the compiler cannot prove
+    uniform becomes a loop over lanes)."""
+    names = re.findall(r"^(_ZN7trimmoe\w*k_(?:ffn|exit)_skinny\w*):", skinny_asm, re.M)
+    assert len(names) == 10
+    for name in names:
+        body = _function(skinny_asm, name)
+        assert not _lds_races(body), name
+        assert not _mfma_lds_hazards(body), name
+        assert not [b for b in body if b.startswith("scratch_")], name
+        for i, b in enumerate(body):
+            if b.startswith("buffer_load") and b.endswith("lds"):
+                assert not any(x.startswith("s_cbranch_execnz") for x in body[i:i + 4]), (name, b)
 
 
 def test_race_checker_finds_planted_races():

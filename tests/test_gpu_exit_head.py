@@ -25,7 +25,9 @@ def _mat(seed, tid, shape, sigma, dtype):
 
 @pytest.mark.parametrize("dtype,V,d,Q", [
     (torch.float32, 1000, 64, 100),
-    (torch.bfloat16, 32128, 768, 50),     # decode-sized: 128 x 32 tiles
+    (torch.bfloat16, 32128, 768, 50),     # decode-sized: weight-streaming, four row tiles
+    (torch.bfloat16, 1003, 64, 1),        # ... K of two k-steps, ragged vocabulary
+    (torch.bfloat16, 20, 2112, 17),       # ... two row tiles, one block
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles, ragged vocabulary
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
 ])

@@ -101,6 +101,24 @@ def test_decode_sized_relu_top1_ragged_up():
     _run_and_compare(cfg)
 
 
+@pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
+    ("swiglu", 1, 1, 1, 64, 64, 0, 1000),       # K of two k-steps: half the wavefronts idle
+    ("relu", 16, 1, 2, 128, 192, 64, 17),       # one full 16-row tile; one row past a group
+    ("swiglu", 17, 2, 2, 192, 320, 0, 128),     # every expert sees 17 rows: a second row tile
+    ("relu", 33, 1, 1, 320, 704, 192, 130),     # a third row tile: the widest streams
+    ("swiglu", 64, 1, 1, 1088, 576, 64, 515),   # the largest batch; clipped last sets
+    ("swiglu", 64, 4, 16, 256, 1408, 128, 3000),
+    ("swiglu", 65, 2, 4, 256, 128, 64, 1000),   # the first batch of the 128-row tiles
+])
+def test_weight_streaming_edges(act, T, k, E, d, F, Fs, V):
+    # decode-sized batches: row tiles of 16, odd column groups per block, and
+    # K quarters of whole, clipped and empty sets
+    cfg = workload("tiny_fp32", dtype="bf16", act=act, n_tokens=T, top_k=k, n_experts=E,
+                   n_local=max(1, E // 2), d_model=d, d_ff=F, d_ff_shared=Fs, vocab_exit=V,
+                   normalize_topk=1, n_layers=3)
+    _run_and_compare(cfg)
+
+
 def test_wide_model_exit_head_ragged():
     # d_model 2048 at 1100 tokens: the exit head takes 256 x 256 tiles with
     # 4 wavefronts; 1100 tokens and 1000 vocabulary rows leave partial token
