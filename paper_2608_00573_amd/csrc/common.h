@@ -79,6 +79,15 @@ constexpr int kSkinnyTokens = 64;
 constexpr int kExitTileBF16 = 256;
 constexpr int kExitTileBF16Small = 128;
 constexpr int kExitTileF32 = 16;
+constexpr int kExitTileF32Mma = 128;
+
+// fp32 rows of K floats that are whole 128-byte K slices run in fp32 MFMAs
+inline bool f32_slices(int K) { return K % 32 == 0; }
+// ... and so do the operands of a head_argmax call, which asks no alignment
+inline bool f32_mma(const void* W, const void* H, int K) {
+  return f32_slices(K) &&
+         ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;
+}
 
 // Operand order of the activations those kernels read: a tile of n <= 16 rows
 // is kept as [k-step of 32][4 groups of 8][n rows][8 elements], so that the
@@ -91,9 +100,12 @@ __host__ __device__ inline int frag_order(int kstep, int group, int row, int n) 
 inline int exit_tile_rows(bool bf16, int T) {
   return bf16 ? (T <= kSkinnyTokens ? kExitTileBF16Small : kExitTileBF16) : kExitTileF32;
 }
-// exit partials per token of a launch on n_cu compute units
-inline int exit_vtiles(bool bf16, int T, int V, int n_cu) {
-  const int rows = exit_tile_rows(bf16, T), n = (V + rows - 1) / rows;
+// exit partials per token of a launch on n_cu compute units (never more than
+// the exit_tile_rows tiles the workspace is sized for); mma_f32: an fp32 head
+// in fp32 MFMAs
+inline int exit_vtiles(bool bf16, bool mma_f32, int T, int V, int n_cu) {
+  const int rows = !bf16 && mma_f32 ? kExitTileF32Mma : exit_tile_rows(bf16, T);
+  const int n = (V + rows - 1) / rows;
   return bf16 && T <= kSkinnyTokens && n > n_cu ? n_cu : n;
 }
 // fp32 GEMM tile

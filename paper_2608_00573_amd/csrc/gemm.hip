@@ -25,7 +25,9 @@
 // head of wide models run on a second bf16 core (4 wavefronts, 256 x 256
 // tiles in v_mfma_f32_16x16x32_bf16; described with its kernels).
 //
-// fp32 path: plain FMA kernels for fp32 models.
+// fp32 path: the first core again with v_mfma_f32_32x32x2_f32 (a K slice is 32
+// floats, the same 128-byte row segments); plain FMA kernels where a row is
+// not a whole number of slices.
 #include <math.h>
 
 #include "gemm.h"
@@ -41,10 +43,12 @@ constexpr int kXcd = 8;      // XCDs of an MI355X; blocks are dealt round-robin
 static_assert(BK == 64, "the LDS layout assumes 128-byte row segments");
 
 // ------------------------------------------------------------ tile shapes --
-// BM x BN block tile, NB B operands sharing A, GM x GN wavefronts
-template <int BM_, int BN_, int NB_, int GM_, int GN_>
+// BM x BN block tile, NB B operands sharing A, GM x GN wavefronts.  F32: the
+// operands are fp32, seen as pairs of 2-byte words (K and strides count words).
+template <int BM_, int BN_, int NB_, int GM_, int GN_, bool F32_ = false>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, NB = NB_, GM = GM_, GN = GN_;
+  static constexpr bool F32 = F32_;
   static constexpr int THREADS = 64 * GM * GN;
   static constexpr int WM = BM / GM, WN = BN / GN;  // wavefront tile
   static constexpr int TM = WM / 32, TN = WN / 32;  // MFMA tiles per wavefront
@@ -223,14 +227,28 @@ struct FragAddr {
 template <class T>
 using Acc = f32x16_t[T::TM][T::TN * T::NB];
 
-// acc[i][j] += A_i B_j^T for the k-step held in f
+// acc[i][j] += A_i B_j^T for the k-step held in f.  fp32: the lane's 16 bytes
+// are four consecutive K of its row; the two half-wavefronts hold neighbouring
+// fours, so MFMA u multiplies K u and 4 + u of the k-step's eight
 template <class T>
 __device__ __forceinline__ void mma_step(const Frags<T>& f, Acc<T>& acc) {
+  if constexpr (T::F32) {
 #pragma unroll
-  for (int i = 0; i < T::TM; ++i)
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int j = 0; j < T::TN * T::NB; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::TN * T::NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4_t, f.a[i])[u],
+                                                           __builtin_bit_cast(f32x4_t, f.b[j])[u],
+                                                           acc[i][j], 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN * T::NB; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+  }
 }
 
 // One slice from stage cur (its k-step-0 fragments already in f0), with the
@@ -456,11 +474,15 @@ struct FfnSrc {
             const float u = acc[i][j][r];
             float v;
             if constexpr (T::NB == 2) {
-              v = silu_mul(acc[i][T::TN + j][r], u);  // gate of the same column
+              const float g = acc[i][T::TN + j][r];  // gate of the same column
+              v = T::F32 ? g / (1.f + expf(-g)) * u : silu_mul(g, u);
             } else {
               v = fmaxf(u, 0.f);
             }
-            static_cast<__bf16*>(a.out)[o] = (__bf16)v;
+            if constexpr (T::F32)
+              static_cast<float*>(a.out)[o] = v;
+            else
+              static_cast<__bf16*>(a.out)[o] = (__bf16)v;
           } else {
             static_cast<float*>(a.out)[d.sp * a.split_stride + o] = acc[i][j][r];
           }
@@ -1139,8 +1161,67 @@ struct ExitSrc {
   __device__ __forceinline__ void epilogue(const Desc& d, Acc<T>& acc) const {
     if constexpr (ARGMAX)
       epilogue_argmax(d, acc);
+    else if constexpr (T::F32)
+      epilogue_softmax_f32(d, acc);
     else
       epilogue_softmax(d, acc);
+  }
+  // fp32 models: the sum of exp(z - max z) with the full-precision exponential
+  // of the difference (a logit's error is not scaled by log2 e before it)
+  __device__ __forceinline__ void epilogue_softmax_f32(const Desc& d, Acc<T>& acc) const {
+    const int v0 = d.mt * T::BM, j0 = d.nt * T::BN;
+    const int a_valid = min(T::BM, a.V - v0);
+    const int b_valid = min(T::BN, n_x - j0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave / T::GN, wn = wave % T::GN;
+    const float ninf = -__builtin_inff();
+#pragma unroll
+    for (int jj = 0; jj < T::TN; ++jj) {
+      float m = ninf;
+#pragma unroll
+      for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = acc_row<T>(wm, i, r, lane);
+          float z = acc[i][jj][r];
+          if (a.bias) z += a.bias[v0 + min(row, a_valid - 1)];
+          z = row < a_valid ? z : ninf;
+          acc[i][jj][r] = z;
+          m = fmaxf(m, z);
+        }
+      {
+        const LanePair pm = lanes_xor32(m);
+        m = fmaxf(pm.a, pm.b);
+      }
+      float sum = 0.f;
+      if (m != ninf) {
+#pragma unroll
+        for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum += expf(acc[i][jj][r] - m);
+      }
+      {
+        const LanePair ps = lanes_xor32(sum);
+        sum = ps.a + ps.b;
+      }
+      if (lane < 32) s_part[wm][acc_col<T>(wn, jj, lane)] = make_float2(m, sum);
+    }
+    lds_barrier();
+    const int c = threadIdx.x;
+    if (c < b_valid) {
+      float M = s_part[0][c].x;
+#pragma unroll
+      for (int g = 1; g < T::GM; ++g) M = fmaxf(M, s_part[g][c].x);
+      float S2 = 0.f;
+#pragma unroll
+      for (int g = 0; g < T::GM; ++g) {
+        const float2 v = s_part[g][c];
+        if (v.y > 0.f) S2 += v.y * expf(v.x - M);
+      }
+      // partials are kept in base 2: (max z * log2 e, sum exp(z - max z))
+      a.partials[(size_t)(j0 + c) * a.n_vtiles + d.mt] =
+          make_float2(M * 1.4426950408889634f, S2);
+    }
   }
   // per (token, vocabulary tile): the largest logit and its vocabulary row
   // (ties to the lower row), the row stored as the float's bit pattern
@@ -1432,6 +1513,12 @@ __global__ __launch_bounds__(big::THREADS) void k_exit_big(ExitArgs a) {
 }
 
 // ------------------------------------------------------------- fp32 path --
+// The FMA kernels below take any K; they read every operand element again per
+// output and run at about 1 TFLOP/s, so rows of whole K slices (f32_slices) go
+// to the first core in fp32 MFMAs instead (Switch-shaped layer, 777 tokens: up
+// 3183 -> 59 us, down 5683 -> 79 us, exit head 31.5 ms -> 366 us, 98 TFLOP/s of
+// the 157 the fp32 matrix rate allows; against an fp64 evaluation the errors of
+// h and xi are those of the FMA kernels, 1.1e-7 and 9e-7).
 constexpr int FT = kF32Tile;
 
 // out[m][n] = X[m] . W[e][n] over a 128-row group tile, 16 columns per block.
@@ -1529,6 +1616,16 @@ using UpDualTile = Tile<kGemmBM, 128, 2, 2, 4>;  // SwiGLU: up and gate share A
 using UpTile = Tile<kGemmBM, 256, 1, 2, 4>;      // ReLU
 using DownTile = Tile<kGemmBM, 256, 1, 2, 4>;
 
+// fp32: two operands of 64 columns or one of 128 per 8 wavefronts, narrower
+// ones for small problems (4 wavefronts at 32 columns)
+template <int BN>
+using UpDualF32 = Tile<kGemmBM, BN, 2, 4, BN / 32, true>;
+template <int BN>
+using FfnF32 = Tile<kGemmBM, BN, 1, BN == 128 ? 2 : 4, BN == 128 ? 4 : BN / 32, true>;
+// exit head: 128 vocabulary rows (kExitTileF32Mma) x 128 or 32 tokens
+using ExitF32 = Tile<kExitTileF32Mma, 128, 1, 4, 2, true>;
+using ExitF32Small = Tile<kExitTileF32Mma, 32, 1, 4, 1, true>;
+
 // K splits of the routed down GEMM, only for a tile bound under two tiles
 // per CU (1, 2 or 4, each split keeping at least 8 K slices): the fewest
 // slices on the busiest CU of a 256-CU persistent grid, and on a tie the
@@ -1610,6 +1707,29 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
       launch_ffn_mma<UpTile, true>(a, max_mt, p.n_cu, st);
     else
       launch_ffn_mma<DownTile, false>(a, max_mt, p.n_cu, st);
+  } else if (f32_slices(K)) {
+    FfnArgs a{static_cast<const bf16_t*>(X), x_idx, static_cast<const bf16_t*>(w0),
+              static_cast<const bf16_t*>(w1), 2 * w_stride, 2 * K, N, p.tiles,
+              &p.counts[kCntTiles], dense, out, p.y_split_stride, 1, act, nullptr, nullptr, nullptr};
+    // the widest tile that still gives every CU one (an fp32 tile is long: 41 us
+    // at 128 x 128 x 768)
+    const auto fills = [&](int bn) { return max_mt * cdiv(N, bn) >= p.n_cu; };
+    if (dual && fills(64))
+      launch_ffn_mma<UpDualF32<64>, true>(a, max_mt, p.n_cu, st);
+    else if (dual)
+      launch_ffn_mma<UpDualF32<32>, true>(a, max_mt, p.n_cu, st);
+    else if (up && fills(128))
+      launch_ffn_mma<FfnF32<128>, true>(a, max_mt, p.n_cu, st);
+    else if (up && fills(64))
+      launch_ffn_mma<FfnF32<64>, true>(a, max_mt, p.n_cu, st);
+    else if (up)
+      launch_ffn_mma<FfnF32<32>, true>(a, max_mt, p.n_cu, st);
+    else if (fills(128))
+      launch_ffn_mma<FfnF32<128>, false>(a, max_mt, p.n_cu, st);
+    else if (fills(64))
+      launch_ffn_mma<FfnF32<64>, false>(a, max_mt, p.n_cu, st);
+    else
+      launch_ffn_mma<FfnF32<32>, false>(a, max_mt, p.n_cu, st);
   } else {
     const dim3 grid(max_mt * cdiv(N, FT));
     if (up)
@@ -1656,6 +1776,16 @@ hipError_t launch_exit_head(const LayerParams& p, bool bf16, hipStream_t st) {
       const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitTile::BN), p.n_cu));
       hipLaunchKernelGGL(k_exit_mma<ExitTile>, grid, dim3(ExitTile::THREADS), 0, st, a);
     }
+  } else if (f32_slices(p.d)) {
+    ExitArgs a{static_cast<const bf16_t*>(p.w_exit), static_cast<const bf16_t*>(p.hx), p.b_exit,
+               &p.counts[kCntExec], p.V, 2 * p.d, p.n_vtiles, p.partials, nullptr};
+    if (p.T <= kSkinnyTokens) {
+      const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitF32Small::BN), p.n_cu));
+      hipLaunchKernelGGL(k_exit_mma<ExitF32Small>, grid, dim3(ExitF32Small::THREADS), 0, st, a);
+    } else {
+      const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitF32::BN), p.n_cu));
+      hipLaunchKernelGGL(k_exit_mma<ExitF32>, grid, dim3(ExitF32::THREADS), 0, st, a);
+    }
   } else {
     const dim3 grid(p.n_vtiles * cdiv(p.T, FT));
     hipLaunchKernelGGL(k_exit_f32<false>, grid, dim3(256), 0, st, static_cast<const float*>(p.w_exit),
@@ -1679,6 +1809,17 @@ hipError_t launch_head_argmax_partials(bool bf16, const void* W, const float* bi
     } else {
       const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitTile::BN), n_cu));
       hipLaunchKernelGGL((k_exit_mma<ExitTile, true>), grid, dim3(ExitTile::THREADS), 0, st, a);
+    }
+  } else if (f32_mma(W, H, K)) {
+    ExitArgs a{static_cast<const bf16_t*>(W), static_cast<const bf16_t*>(H), bias, n_rows_dev, V,
+               2 * K, n_vtiles, partials};
+    if (n_rows <= kSkinnyTokens) {
+      const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitF32Small::BN), n_cu));
+      hipLaunchKernelGGL((k_exit_mma<ExitF32Small, true>), grid, dim3(ExitF32Small::THREADS), 0, st,
+                         a);
+    } else {
+      const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitF32::BN), n_cu));
+      hipLaunchKernelGGL((k_exit_mma<ExitF32, true>), grid, dim3(ExitF32::THREADS), 0, st, a);
     }
   } else {
     const dim3 grid(n_vtiles * cdiv(n_rows, FT));

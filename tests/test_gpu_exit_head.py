@@ -24,7 +24,9 @@ def _mat(seed, tid, shape, sigma, dtype):
 
 
 @pytest.mark.parametrize("dtype,V,d,Q", [
-    (torch.float32, 1000, 64, 100),
+    (torch.float32, 1000, 64, 100),       # 128 x 128 fp32 tiles
+    (torch.float32, 300, 96, 7),          # 128 x 32 fp32 tiles
+    (torch.float32, 16, 40, 33),          # rows of partial K slices
     (torch.bfloat16, 32128, 768, 50),     # decode-sized: weight-streaming, four row tiles
     (torch.bfloat16, 1003, 64, 1),        # ... K of two k-steps, ragged vocabulary
     (torch.bfloat16, 20, 2112, 17),       # ... two row tiles, one block
@@ -40,6 +42,18 @@ def test_head_argmax_matches_oracle(dtype, V, d, Q):
     clear = margin > 1e-5       # fp32 accumulation of the same stored values
     assert clear.mean() > 0.99
     assert np.array_equal(got[clear], want[clear])
+
+
+def test_head_argmax_of_unaligned_fp32_operands():
+    # fp32 operands need no alignment: an odd offset takes the FMA kernel
+    W, Wn = _mat(13, 1, (10, 64), 0.02, torch.float32)
+    H, Hn = _mat(14, 2, (20, 64), 1.0, torch.float32)
+    buf = torch.empty(1 + H.numel(), dtype=torch.float32, device=DEV)
+    Hd = buf[1:].view(H.shape)
+    Hd.copy_(H)
+    assert Hd.data_ptr() % 16 != 0
+    got = abi.trimmoe_head_argmax(W.to(DEV), Hd).cpu().numpy()
+    assert np.array_equal(got, X.head_argmax(Wn, Hn)[0])
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

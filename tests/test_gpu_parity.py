@@ -119,6 +119,24 @@ def test_weight_streaming_edges(act, T, k, E, d, F, Fs, V):
     _run_and_compare(cfg)
 
 
+@pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
+    ("relu", 64, 1, 8, 64, 256, 0, 130),        # two K slices; a partial vocabulary tile
+    ("swiglu", 65, 2, 4, 96, 160, 64, 1),       # three slices; the 128-token exit tile
+    ("relu", 300, 1, 2, 32, 2080, 0, 300),      # one slice; 64-column tiles, ragged rows
+    ("swiglu", 300, 1, 2, 64, 4128, 96, 257),   # 64-column SwiGLU tiles with a remainder
+    ("relu", 300, 1, 4, 64, 8224, 0, 100),      # 128-column tiles with a remainder
+    ("swiglu", 130, 2, 4, 64, 100, 33, 70),     # F and Fs of partial slices: FMA down kernels
+    ("relu", 40, 1, 4, 40, 64, 0, 70),          # d of a partial slice: FMA up and exit kernels
+])
+def test_fp32_tiles(act, T, k, E, d, F, Fs, V):
+    # fp32 models: the fp32 MFMA tiles at their widths and remainders, and the
+    # FMA kernels of rows that are not whole K slices
+    cfg = workload("tiny_fp32", act=act, n_tokens=T, top_k=k, n_experts=E, n_local=max(1, E // 2),
+                   d_model=d, d_ff=F, d_ff_shared=Fs, vocab_exit=V, normalize_topk=1, n_layers=3,
+                   conf_mode="sigmoid" if V == 1 else "softmax")
+    _run_and_compare(cfg)
+
+
 def test_wide_model_exit_head_ragged():
     # d_model 2048 at 1100 tokens: the exit head takes 256 x 256 tiles with
     # 4 wavefronts; 1100 tokens and 1000 vocabulary rows leave partial token
