@@ -241,7 +241,7 @@ void fill_params(LayerParams& P, const trimmoe_model* m, int l, const trimmoe_po
   P.horizon = std::min(pol->horizon, m->n_layers - l);
   P.la_subs = P.horizon > 1 ? pol->la_subs : 1;
   P.trans_b = m->trans_b;
-  P.rb = route_block_tokens(T, P.horizon > 1);
+  P.rb = route_block_tokens(T, P.horizon > 1, m->n_experts);
   P.bm = expert_tile_rows(m->dtype == TRIMMOE_BF16, T, k, m->n_experts, m->d_model, m->d_ff);
   // the large-group down GEMM cuts the tiles of its last round along K
   // instead of splitting every tile

@@ -17,13 +17,29 @@ typedef uint16_t bf16_t;
 constexpr int kRouteTokens = 32;
 // route blocks the look-ahead aims for: one per CU
 constexpr int kLookaheadBlocks = 256;
+// route blocks a batch without look-ahead is dealt to at most (while that
+// leaves kRouteTokens or fewer a block)
+constexpr int kRouteBlocks = 128;
+// bounds of the scan inside the bucket kernel: block histogram entries (route
+// blocks x experts) and route blocks a bucket block holds in LDS
+constexpr int kFusedScanEntries = 4096;
+constexpr int kFusedScanBlocks = 1024;
 
-// tokens per route block for a batch of T tokens: kRouteTokens, or with
-// look-ahead the power of two that gives about kLookaheadBlocks blocks
-inline int route_block_tokens(int T, bool lookahead) {
-  if (!lookahead) return kRouteTokens;
-  int rb = 1;
-  while (rb < kRouteTokens && 2 * rb * kLookaheadBlocks <= T) rb *= 2;
+// tokens per route block for a batch of T tokens: the power of two that gives
+// about a block per CU, at most kRouteTokens.  Without look-ahead at least
+// kRouteTokensMin: every block reads the router weights and the Sim table
+// again, and its top-k takes kRouteTokensMin tokens (one a wavefront) at once
+constexpr int kRouteTokensMin = 8;
+inline int route_block_tokens(int T, bool lookahead, int E) {
+  int rb = lookahead ? 1 : kRouteTokensMin;
+  if (lookahead) {
+    while (rb < kRouteTokens && 2 * rb * kLookaheadBlocks <= T) rb *= 2;
+  } else {
+    // ... and no more blocks than keep the scan in the bucket kernel
+    while (rb < kRouteTokens &&
+           (rb * kRouteBlocks < T || (long long)((T + rb - 1) / rb) * E > kFusedScanEntries))
+      rb *= 2;
+  }
   return rb;
 }
 // route blocks the workspace provides for batches of up to T tokens

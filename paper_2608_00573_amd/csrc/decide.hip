@@ -21,12 +21,9 @@
 // (34), Sec. V-C).
 #include <math.h>
 
-#include "common.h"
+#include "gemm.h"
 
 namespace trimmoe {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int RB = kRouteTokens;
 constexpr int KMAX = TRIMMOE_MAX_TOPK;
@@ -69,47 +66,120 @@ __global__ void k_trace_fill(LayerParams p) {
 // ------------------------------------------- route + decide (one layer) --
 constexpr int kRouteWaves = 8;  // wavefronts of a route block
 
-// K splits of the router logits: enough (column tile, K range) items for the
-// wavefronts of a route block, each range a multiple of 32
-static __host__ __device__ inline int route_ks(int E, int d) {
-  const int nct = (E + 15) / 16;
-  int ks = 1;
-  while (nct * ks < kRouteWaves) ks *= 2;
-  while (ks > 1 && d % (32 * ks) != 0) ks /= 2;
-  return ks;
+// The value of the lane OFF apart (l ^ OFF) for reductions whose steps run
+// OFF = 1, 2, 4, ... and leave every group of OFF lanes uniform: DPP and the
+// permlane swaps (VALU) instead of LDS lane exchanges, whose latency made up
+// most of the routing's reductions.  The mirrors of 8 and 16 lanes reach the
+// other half of their group, which is all a uniform half needs.
+template <int OFF>
+__device__ __forceinline__ float group_other(float v) {
+  const int x = __float_as_int(v);
+  if constexpr (OFF == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, false));
+  if constexpr (OFF == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0x4e, 0xf, 0xf, false));
+  if constexpr (OFF == 4) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0x141, 0xf, 0xf, false));
+  if constexpr (OFF == 8) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0x140, 0xf, 0xf, false));
+  const bool odd = threadIdx.x & OFF;  // OFF = 16, 32: which of the pair is the other lane's
+  const LanePair p = OFF == 16 ? lanes_xor16(v) : lanes_xor32(v);
+  return odd ? p.a : p.b;
 }
+template <int OFF>
+__device__ __forceinline__ int group_other(int v) {
+  return __float_as_int(group_other<OFF>(__int_as_float(v)));
+}
+
+// runs step.run<OFF>() for OFF = 1, 2, ... below G (a power of two up to 64;
+// the same in every lane)
+template <class Step>
+__device__ __forceinline__ void group_steps(int G, Step step) {
+  if (G > 1) step.template run<1>();
+  if (G > 2) step.template run<2>();
+  if (G > 4) step.template run<4>();
+  if (G > 8) step.template run<8>();
+  if (G > 16) step.template run<16>();
+  if (G > 32) step.template run<32>();
+}
+
+// the least (q, j), j == none: no candidate
+struct LeastStep {
+  float& q;
+  int& j;
+  int none;
+  template <int OFF>
+  __device__ __forceinline__ void run() {
+    const float oq = group_other<OFF>(q);
+    const int oj = group_other<OFF>(j);
+    if (oj < none && (j == none || oq < q || (oq == q && oj < j))) {
+      j = oj;
+      q = oq;
+    }
+  }
+};
+// the largest (v, lower j), j == none: no candidate
+struct LargestStep {
+  float& v;
+  int& j;
+  int none;
+  template <int OFF>
+  __device__ __forceinline__ void run() {
+    const float ov = group_other<OFF>(v);
+    const int oj = group_other<OFF>(j);
+    if (oj < none && (j == none || ov > v || (ov == v && oj < j))) {
+      j = oj;
+      v = ov;
+    }
+  }
+};
+struct SumStep {
+  float& v;
+  template <int OFF>
+  __device__ __forceinline__ void run() {
+    v += group_other<OFF>(v);
+  }
+};
 
 // Eq. (3): best local substitute c(e) = argmin over local j != e with
 // Sim[e][j] >= sim_min of Q(e, j) = min(1, phi_scale (1 - Sim[e][j]) / 2),
-// ties to the lower j (-1: none), and its Q.  One wavefront per row e: each
-// lane scans j = lane, lane + 64, ... in order, then a butterfly takes the
-// least (Q, j) pair, which is what a serial scan that keeps the first least
-// Q returns (Q is never NaN: fminf(1, NaN) = 1).  Every lane gets the result.
-__device__ inline void best_substitute(const float* sim, const uint8_t* local, int E, int e,
-                                       float phi_scale, float sim_min, int lane, int& c,
-                                       float& q) {
+// ties to the lower j (-1: none), and its Q, for every expert e at once: the
+// 512 threads of a route block are dealt G to a row (512 over the power of two
+// above E, at most 64).  Each lane scans j = g, g + G, ... in order (the loads
+// of eight candidates in flight together), then the group takes the least
+// (Q, j), which is what a serial scan that keeps the first least Q returns (Q
+// is never NaN: fminf(1, NaN) = 1).
+__device__ inline void substitute_table(const float* sim, const uint8_t* local, int E,
+                                        float phi_scale, float sim_min, int16_t* c, float* q) {
+  int ep = 1;
+  while (ep < E) ep <<= 1;
+  const int G = min(64, (int)blockDim.x / ep);
+  const int e = threadIdx.x / G, g = threadIdx.x & (G - 1);
+  if (e >= E) return;  // whole groups leave together
   int best = E;
   float bq = 0.f;
-  for (int j = lane; j < E; j += 64) {
-    const float sv = sim[(size_t)e * E + j];
-    if (j == e || !local[j] || !(sv >= sim_min)) continue;
-    const float qj = fminf(1.f, phi_scale * (1.f - sv) * 0.5f);
-    if (best == E || qj < bq) {
-      best = j;
-      bq = qj;
-    }
-  }
+  constexpr int CH = 8;
+  for (int j0 = g; j0 < E; j0 += CH * G) {
+    float sv[CH];
+    uint8_t lm[CH];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float oq = __shfl_xor(bq, off);
-    const int oj = __shfl_xor(best, off);
-    if (oj < E && (best == E || oq < bq || (oq == bq && oj < best))) {
-      best = oj;
-      bq = oq;
+    for (int u = 0; u < CH; ++u) {
+      const int j = min(j0 + u * G, E - 1);
+      sv[u] = sim[(size_t)e * E + j];
+      lm[u] = local[j];
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int j = j0 + u * G;
+      if (j >= E || j == e || !lm[u] || !(sv[u] >= sim_min)) continue;
+      const float qj = fminf(1.f, phi_scale * (1.f - sv[u]) * 0.5f);
+      if (best == E || qj < bq) {
+        best = j;
+        bq = qj;
+      }
     }
   }
-  c = best < E ? best : -1;
-  q = best < E ? bq : 0.f;
+  group_steps(G, LeastStep{bq, best, E});
+  if (g == 0) {
+    c[e] = (int16_t)(best < E ? best : -1);
+    q[e] = best < E ? bq : 0.f;
+  }
 }
 
 // Under look-ahead a remote slot may run its target or any of its local
@@ -136,15 +206,7 @@ __device__ inline void best_candidates(const float* sim, const uint8_t* local, i
         bq = qj;
       }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const float oq = __shfl_xor(bq, off);
-      const int oj = __shfl_xor(best, off);
-      if (oj < E && (best == E || oq < bq || (oq == bq && oj < best))) {
-        best = oj;
-        bq = oq;
-      }
-    }
+    group_steps(64, LeastStep{bq, best, E});
     if (lane == 0) {
       c[r] = (int16_t)(best < E ? best : -1);
       q[r] = best < E ? bq : 0.f;
@@ -363,6 +425,173 @@ __host__ __device__ inline size_t la_carve(char* base, int E, int B, int k, int 
   return off;
 }
 
+// -------------------------------------------------------- router logits --
+// A route block's logits of up to 32 tokens x E experts, K split over its
+// wavefronts.  Loaded straight into MFMA operands, neighbouring lanes read
+// different rows, and the four-fold address cycles of that bound the block (49 K
+// cycles at E = 60, d = 2048).  So the rows go to LDS by DMA with lanes along
+// them, in slices of KS k-steps (64 bytes of every row each), through a ring of
+// NST stages: one barrier per slice, NST - 1 slices in flight.  A stage holds
+// the token rows, then the expert rows, 16-byte chunks swizzled so that
+// fragment reads spread over the banks.  Whole kernel on an MI355X, against
+// direct operand loads, LDS lane exchanges and 32-token blocks (us): Qwen
+// shapes 72 -> 23 at 16 tokens, 90 -> 39 at 4099; Mixtral 27 -> 15 at 32, 27 ->
+// 17 at 333, 31 -> 30 at 8192; fp32 at the Switch shape, 777 tokens, 74 -> 17
+// (serial FMA logits before); Switch at 4096 12 -> 12 (latency of its launch).
+template <int KS>
+struct LogitRing {
+  static constexpr int SB = KS * 64;                     // bytes of a row segment
+  static constexpr int CPR = SB / 16, RPI = 64 / CPR;    // chunks per row, rows per DMA
+  static constexpr int ROWS = KS == 16 ? 32 : KS == 8 ? 48 : KS == 4 ? 96 : 288;
+  static constexpr int NPW = (ROWS / RPI + kRouteWaves - 1) / kRouteWaves;  // DMAs per wavefront
+  static constexpr int STAGE = NPW * kRouteWaves * 1024;
+  static constexpr int NST = KS == 2 ? 2 : KS == 16 ? 3 : 4;
+  static constexpr int BYTES = NST * STAGE;
+};
+constexpr int kLogitRing = 96 * 1024;
+static_assert(LogitRing<16>::BYTES <= kLogitRing && LogitRing<8>::BYTES <= kLogitRing && LogitRing<4>::BYTES <= kLogitRing &&
+                  LogitRing<2>::BYTES <= kLogitRing,
+              "one ring size");
+
+// K splits of the logits (partial sums in LDS): wavefront w takes expert
+// column tile w % nct and every splits-th k-step of a slice
+static __host__ __device__ inline int logit_splits(int E) {
+  const int nct = (E + 15) / 16;
+  return nct < kRouteWaves ? kRouteWaves / nct : 1;
+}
+
+template <bool F32, int KS>
+__device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, char* ring, int base,
+                                             int nt) {
+  using R = LogitRing<KS>;
+  constexpr int ES = F32 ? 4 : 2;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int E = p.E, nct = (E + 15) >> 4, splits = logit_splits(E);
+  const int hr = nt > 16 ? 32 : 16;          // token rows of a stage
+  const int n_dma = (hr + 16 * nct) / R::RPI;
+  const int rowb = p.d * ES;                 // bytes of a row, a multiple of 64
+  const int n_step = rowb / 64, n_slice = (n_step + KS - 1) / KS;
+  // source rows of this thread's DMAs (past the tokens or experts: a valid row
+  // again, never used; past the stage's rows: the last DMA again)
+  const char* src[R::NPW];
+  int ch[R::NPW], dst[R::NPW];
+#pragma unroll
+  for (int i = 0; i < R::NPW; ++i) {
+    const int q = min(wave * R::NPW + i, n_dma - 1);
+    const int row = q * R::RPI + lane / R::CPR;
+    dst[i] = __builtin_amdgcn_readfirstlane(q) * 1024;
+    ch[i] = ((lane % R::CPR) ^ swz16(row)) * 16;
+    if (row < hr)
+      src[i] = static_cast<const char*>(p.h) + (size_t)p.active_idx[base + min(row, nt - 1)] * rowb;
+    else
+      src[i] = static_cast<const char*>(p.w_router) + (size_t)min(row - hr, E - 1) * rowb;
+  }
+  auto dma = [&](int g) {
+    char* st = ring + (g % R::NST) * R::STAGE;
+#pragma unroll
+    for (int i = 0; i < R::NPW; ++i) {
+      // past the end of K: the last chunk again (never used)
+      const int off = min(g * R::SB + ch[i], rowb - 16);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[i] + off),
+                                       (lds_byte*)(st + dst[i]), 16, 0, 0);
+    }
+  };
+  const int fr = lane & 15, hq = lane >> 4;
+  const uint32_t ring0 = (uint32_t)(uintptr_t)(const lds_byte*)ring;
+  f32x4_t acc[2][2] = {};  // [expert tile of this wavefront][token tile]
+  const int kq = wave / nct;
+  const bool busy = nct >= kRouteWaves || kq < splits;
+  const int s_first = nct >= kRouteWaves ? 0 : kq;
+  const bool whole = n_slice < R::NST;  // a short K is all in flight at once
+#pragma unroll
+  for (int g = 0; g < R::NST - 1; ++g) dma(g);
+  if (whole) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  for (int g = 0; g < n_slice; ++g) {
+    if (!whole) {
+      // slice g has landed here and, after the barrier, everywhere; every
+      // wavefront is past its reads of slice g - 1, whose stage is refilled
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(R::NPW * (R::NST - 2)) : "memory");
+      dma(g + R::NST - 1);
+    }
+    if (!busy) continue;
+    const uint32_t st = ring0 + (g % R::NST) * R::STAGE;
+    for (int s = s_first; s < KS && g * KS + s < n_step; s += splits) {
+      auto addr = [&](int row) {
+        return st + row * R::SB + (((4 * s + hq) ^ swz16(row)) << 4);
+      };
+      const uint32_t a0 = addr(fr), a1 = addr(hr == 32 ? 16 + fr : fr);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int ct = nct >= kRouteWaves ? wave + kRouteWaves * t : wave % nct;
+        if (t == 1 && (nct < kRouteWaves || ct >= nct)) continue;
+        bf16x8_t x0, x1, w;
+        // (the reads wait in their own statement: the compiler would wait for
+        // every DMA in flight before a read it sees)
+        asm volatile(
+            "ds_read_b128 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %5\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(x0), "=&v"(x1), "=&v"(w)
+            : "v"(a0), "v"(a1), "v"(addr(hr + 16 * ct + fr))
+            : "memory");
+        if constexpr (F32) {
+          // the lane's four K of the step; lane groups hold neighbouring fours
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float wv = __builtin_bit_cast(f32x4_t, w)[u];
+            acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4_t, x0)[u], wv,
+                                                             acc[t][0], 0, 0, 0);
+            acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4_t, x1)[u], wv,
+                                                             acc[t][1], 0, 0, 0);
+          }
+        } else {
+          acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, w, acc[t][0], 0, 0, 0);
+          acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, w, acc[t][1], 0, 0, 0);
+        }
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // DMAs past the end, into the ring
+  // accumulator: column = lane % 16 (expert), row = 4 (lane / 16) + r (token)
+  if (busy) {
+    float* dz = zs + (nct >= kRouteWaves ? 0 : (size_t)kq * RB * E);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int ct = nct >= kRouteWaves ? wave + kRouteWaves * t : wave % nct;
+      if (t == 1 && (nct < kRouteWaves || ct >= nct)) continue;
+      const int e = ct * 16 + fr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 4 * hq + r;
+        if (e < E && row < nt) dz[row * E + e] = acc[t][0][r];
+        if (e < E && 16 + row < nt) dz[(16 + row) * E + e] = acc[t][1][r];
+      }
+    }
+  }
+  __syncthreads();
+  if (splits > 1) {
+    for (int idx = threadIdx.x; idx < nt * E; idx += blockDim.x) {
+      float v = zs[idx];
+      for (int q = 1; q < splits; ++q) v += zs[(size_t)q * RB * E + idx];
+      zs[idx] = v;
+    }
+  }
+}
+
+// logits of a block: by column tiles, so that a slice has a k-step per split
+template <bool F32>
+__device__ __forceinline__ void route_logits_any(const LayerParams& p, float* zs, char* ring,
+                                                 int base, int nt) {
+  const int nct = (p.E + 15) >> 4;
+  if (nct == 1 && p.rb <= 16)
+    route_logits<F32, 16>(p, zs, ring, base, nt);
+  else if (nct == 1)
+    route_logits<F32, 8>(p, zs, ring, base, nt);
+  else if (nct <= 4)
+    route_logits<F32, 4>(p, zs, ring, base, nt);
+  else
+    route_logits<F32, 2>(p, zs, ring, base, nt);
+}
+
 // One block = RB active tokens.  Phase 0: the layer's substitute table
 // (and, with look-ahead, the later layers' tables and transitions), one
 // wavefront per expert row.  Phase 1: router logits into LDS (MFMA 16x16x32
@@ -374,7 +603,7 @@ __host__ __device__ inline size_t la_carve(char* base, int E, int B, int k, int 
 // for the bucketing.
 template <bool BF16, bool LA>
 __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
-  extern __shared__ float zs[];  // [route_ks][RB][E] logits, K partial sums; then LaLds
+  extern __shared__ __align__(16) float zs[];  // [logit_splits][RB][E] logits, K partial sums; LaLds
   __shared__ int s_cnt[TRIMMOE_MAX_EXPERTS];
   __shared__ int16_t s_subc[TRIMMOE_MAX_EXPERTS];  // best substitute (H = 1)
   __shared__ float s_subq[TRIMMOE_MAX_EXPERTS];
@@ -412,15 +641,33 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
     budget_pre = p.budget_tok ? p.budget_tok[t_pre] : p.budget;
   }
 
-  // Eq. (3): the layer's substitute table, one wavefront per expert
+  // Eq. (3): the layer's substitute table
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int e = wave; e < E; e += kRouteWaves) {
-    int c;
-    float q;
-    best_substitute(p.sim, p.local_mask, E, e, p.phi_scale, p.sim_min, lane, c, q);
-    if (lane == 0) {
-      s_subc[e] = (int16_t)c;
-      s_subq[e] = q;
+  substitute_table(p.sim, p.local_mask, E, p.phi_scale, p.sim_min, s_subc, s_subq);
+
+  // router logits: the ring lies beside the partial sums, under look-ahead in
+  // the dynamic LDS, whose tables are built after it
+  if (BF16 || d % 16 == 0) {
+    if constexpr (LA) {
+      char* ring = reinterpret_cast<char*>(zs + (size_t)logit_splits(E) * RB * E);
+      static_assert(RB % 4 == 0, "the ring stays 16-byte aligned");
+      route_logits_any<!BF16>(p, zs, ring, base, nt);
+    } else {
+      __shared__ __align__(16) char ring[kLogitRing];
+      route_logits_any<!BF16>(p, zs, ring, base, nt);
+    }
+  } else {
+    // fp32 rows that are not whole 64-byte steps
+    const float* h = static_cast<const float*>(p.h);
+    const float* W = static_cast<const float*>(p.w_router);
+    for (int idx = threadIdx.x; idx < nt * E; idx += blockDim.x) {
+      const int i = idx / E, e = idx % E;
+      const int t = p.active_idx[base + i];
+      const float* hr = h + (size_t)t * d;
+      const float* wr = W + (size_t)e * d;
+      float acc = 0.f;
+      for (int j = 0; j < d; ++j) acc = fmaf(hr[j], wr[j], acc);
+      zs[i * E + e] = acc;
     }
   }
 
@@ -429,8 +676,9 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
   const int nlev = LA ? p.horizon - 1 : 0;
   if constexpr (LA) {
     const int B = p.trans_b, C = p.la_subs;
-    const int ks = BF16 ? route_ks(E, d) : 1;
-    la_carve(reinterpret_cast<char*>(zs + (size_t)ks * RB * E), E, B, k, nlev, C, &la);
+    // (over the partial sums and the ring, which are done with)
+    __syncthreads();
+    la_carve(reinterpret_cast<char*>(zs + (size_t)RB * E), E, B, k, nlev, C, &la);
     // this layer's candidate lists, then the later layers': placement,
     // candidate lists, theta and slope; the transitions out of this layer
     // and every later one but the last
@@ -458,108 +706,6 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
                 la.theta, la.slope, p.omega_t, 1.f - p.omega_t, p.t_local, p.t_remote};
   }
 
-  if constexpr (BF16) {
-    // logits of RB = 32 tokens x E experts with 16x16x32 MFMAs: a wavefront
-    // takes one 16-expert column tile and one K range for both 16-token row
-    // tiles, so each expert row is read once per 32 tokens.  With few column
-    // tiles the K range is split (route_ks) so that all wavefronts work;
-    // the partial sums are added in K order.  The k-steps run in groups of
-    // four whose loads are issued one group ahead (clamped to the last group:
-    // in bounds, unused).  Rows past the live tokens / experts load a clamped
-    // valid row (never stored).
-    const bf16_t* h = static_cast<const bf16_t*>(p.h);
-    const bf16_t* W = static_cast<const bf16_t*>(p.w_router);
-    const int nct = (E + 15) >> 4, ks = route_ks(E, d), dk = d / ks;
-    const int tl = lane & 15, kl = 8 * (lane >> 4);
-    const int t0 = p.active_idx[base + min(tl, nt - 1)];
-    const int t1 = p.active_idx[base + min(16 + tl, nt - 1)];
-    for (int w = wave; w < nct * ks; w += kRouteWaves) {
-      const int ct = w % nct, kq = w / nct;
-      const int e = ct * 16 + tl;
-      const bf16_t* h0 = h + (size_t)t0 * d + kq * dk + kl;
-      const bf16_t* h1 = h + (size_t)t1 * d + kq * dk + kl;
-      const bf16_t* wr = W + (size_t)min(e, E - 1) * d + kq * dk + kl;
-      f32x4_t acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-      const int ng = dk / 128;  // full groups of four k-steps
-      if (ng > 0) {
-        bf16x8_t a0[4], a1[4], b[4], n0[4], n1[4], nb[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          a0[u] = *reinterpret_cast<const bf16x8_t*>(h0 + 32 * u);
-          a1[u] = *reinterpret_cast<const bf16x8_t*>(h1 + 32 * u);
-          b[u] = *reinterpret_cast<const bf16x8_t*>(wr + 32 * u);
-        }
-        for (int g = 0; g < ng; ++g) {
-          const int o = min(g + 1, ng - 1) * 128;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            n0[u] = *reinterpret_cast<const bf16x8_t*>(h0 + o + 32 * u);
-            n1[u] = *reinterpret_cast<const bf16x8_t*>(h1 + o + 32 * u);
-            nb[u] = *reinterpret_cast<const bf16x8_t*>(wr + o + 32 * u);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[u], b[u], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[u], b[u], acc1, 0, 0, 0);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            a0[u] = n0[u];
-            a1[u] = n1[u];
-            b[u] = nb[u];
-          }
-        }
-      }
-      // the remaining 0..3 k-steps: every load issued before the first MFMA
-      // (offsets clamped to the last k-step: in bounds; their MFMAs are skipped)
-      const int rem = (dk - ng * 128) / 32;
-      if (rem > 0) {
-        bf16x8_t a0[3], a1[3], b[3];
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          const int o = ng * 128 + 32 * min(u, rem - 1);
-          a0[u] = *reinterpret_cast<const bf16x8_t*>(h0 + o);
-          a1[u] = *reinterpret_cast<const bf16x8_t*>(h1 + o);
-          b[u] = *reinterpret_cast<const bf16x8_t*>(wr + o);
-        }
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          if (u < rem) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[u], b[u], acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[u], b[u], acc1, 0, 0, 0);
-          }
-        }
-      }
-      // accumulator: column = lane % 16 (expert), row = 4 * (lane / 16) + r (token)
-      float* dst = zs + (size_t)kq * RB * E;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 4 * (lane >> 4) + r;
-        if (e < E && row < nt) dst[row * E + e] = acc0[r];
-        if (e < E && 16 + row < nt) dst[(16 + row) * E + e] = acc1[r];
-      }
-    }
-    if (ks > 1) {
-      __syncthreads();
-      for (int idx = threadIdx.x; idx < nt * E; idx += blockDim.x) {
-        float v = zs[idx];
-        for (int q = 1; q < ks; ++q) v += zs[(size_t)q * RB * E + idx];
-        zs[idx] = v;
-      }
-    }
-  } else {
-    const float* h = static_cast<const float*>(p.h);
-    const float* W = static_cast<const float*>(p.w_router);
-    for (int idx = threadIdx.x; idx < nt * E; idx += blockDim.x) {
-      const int i = idx / E, e = idx % E;
-      const int t = p.active_idx[base + i];
-      const float* hr = h + (size_t)t * d;
-      const float* wr = W + (size_t)e * d;
-      float acc = 0.f;
-      for (int j = 0; j < d; ++j) acc = fmaf(hr[j], wr[j], acc);
-      zs[i * E + e] = acc;
-    }
-  }
   __syncthreads();
 
   // Eq. (4) per token, G lanes per token (G the least power of two >= E, at
@@ -567,7 +713,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
   // experts e = g, g + G, ...: biased logits (NaN ranks last), the top-k in
   // rank order (larger logit first, ties to the lower id; each pick is the
   // best logit ranked strictly after the previous one) and the softmax
-  // weights of the picks.  Butterflies stay inside the lane group.
+  // weights of the picks.  Reductions stay inside the lane group.
   {
     int G = 1;
     while (G < E && G < 64) G <<= 1;
@@ -596,16 +742,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
             bv = v;
           }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          if (off >= G) continue;
-          const float ov = __shfl_xor(bv, off);
-          const int oe = __shfl_xor(be, off);
-          if (oe < E && (be == E || ov > bv || (ov == bv && oe < be))) {
-            be = oe;
-            bv = ov;
-          }
-        }
+        group_steps(G, LargestStep{bv, be, E});
         if (g == 0) sS[ti][r] = be < E ? be : -1;
         vtop[r] = bv;
         vprev = bv;
@@ -616,9 +753,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
       const float zmax = vtop[0];
       float sum = 0.f;
       for (int e = g; e < E; e += G) sum += expf(z[e] - zmax);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1)
-        if (off < G) sum += __shfl_xor(sum, off);
+      group_steps(G, SumStep{sum});
       if (g == 0) {
         float imp = 0.f;
 #pragma unroll
@@ -636,14 +771,127 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
   }
   __syncthreads();
 
+  if constexpr (!LA) {
+    // H = 1: every slot's resolution in registers (loops over the slots are
+    // unrolled; LDS and dynamically indexed arrays made this one thread per
+    // token the longest chain of a small block)
+    const int i = threadIdx.x;
+    if (i < nt) {
+      const int pos = base + i, t = t_pre;
+      const float I = sI[i], D = d_pre, budget = budget_pre;
+      const float wt = p.omega_t, wd = 1.f - p.omega_t;
+      int e[KMAX], x[KMAX];
+      float w[KMAX], q[KMAX];
+      unsigned loc = 0, can = 0;  // slots with a local target; remote ones whose substitute fits
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r) {
+        e[r] = r < k ? sS[i][r] : 0;
+        w[r] = r < k ? sW[i][r] : 0.f;
+        x[r] = s_subc[e[r]];
+        q[r] = s_subq[e[r]];
+        if (r < k) {
+          if (s_local[e[r]])
+            loc |= 1u << r;
+          else if (x[r] >= 0 && D + q[r] <= budget)
+            can |= 1u << r;
+        }
+      }
+      const int n_loc = __popc(loc), n_rem = k - n_loc;
+      // Eq. (34) + Eq. (31): every subset of the substitutable remote slots
+      // within the budget, in ascending bitmask order
+      float bf = 0.f, bsq = 0.f;
+      int bns = 0;
+      unsigned bmask = 0, m = 0;
+      bool have = false, all_local = false;
+      for (;;) {
+        float sq = 0.f;
+#pragma unroll
+        for (int r = 0; r < KMAX; ++r)
+          if ((m >> r) & 1) sq += q[r];
+        if (D + sq <= budget) {
+          const int ns = __popc(m);
+          if (ns == n_rem) all_local = true;
+          const float f =
+              wt * ((float)(n_loc + ns) * p.t_local + (float)(n_rem - ns) * p.t_remote) +
+              (budget > 0.f ? wd * sq / budget : 0.f);
+          if (!have || f < bf || (f == bf && (ns < bns || (ns == bns && m < bmask)))) {
+            have = true;
+            bf = f;
+            bns = ns;
+            bmask = m;
+            bsq = sq;
+          }
+        }
+        m = (m - can) & can;
+        if (m == 0) break;
+      }
+      // Eq. (35) + importance threshold + Eq. (32): skip admission and choice
+      const float lam = fminf(1.f, p.skip_slope * I);
+      bool skip = false;
+      if (!all_local && I <= p.theta && D + lam <= budget)
+        skip = (budget > 0.f ? wd * lam / budget : 0.f) < bf;
+      if (!have) skip = false;  // unreachable: the empty assignment is feasible
+
+      // experts run; a substitute keeps its target's weight, and duplicates
+      // merge into the first slot that runs the expert, in rank order
+      unsigned dup = 0;
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r) {
+        const bool sub = (bmask >> r) & 1;
+        const int kind = skip ? TRIMMOE_KIND_NONE
+                         : sub ? TRIMMOE_KIND_SUBST
+                         : (loc >> r) & 1 ? TRIMMOE_KIND_LOCAL : TRIMMOE_KIND_REMOTE;
+        if (!sub) x[r] = e[r];
+        if (r < k) {
+          if (p.tr_target) p.tr_target[(size_t)t * k + r] = (int16_t)e[r];
+          if (p.tr_exec) p.tr_exec[(size_t)t * k + r] = (int16_t)(skip ? -1 : x[r]);
+          if (p.tr_kind) p.tr_kind[(size_t)t * k + r] = (int8_t)kind;
+          if (p.tr_gate) p.tr_gate[(size_t)t * k + r] = w[r];
+        }
+#pragma unroll
+        for (int j = 0; j < r; ++j)
+          if (r < k && !((dup >> r) & 1) && x[j] == x[r]) {
+            dup |= 1u << r;
+            w[j] += w[r];
+          }
+      }
+      int n = 0;
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r)
+        if (r < k && !skip && !((dup >> r) & 1)) {
+          p.tok_exec[(size_t)pos * k + n] = x[r];
+          p.tok_w[(size_t)pos * k + n] = w[r];
+          atomicAdd(&s_cnt[x[r]], 1);
+          ++n;
+        }
+      for (; n < k; ++n) {
+        p.tok_exec[(size_t)pos * k + n] = -1;
+        p.tok_w[(size_t)pos * k + n] = 0.f;
+      }
+      const float dnew = D + (skip ? lam : bsq);  // Eq. (41) / (42)
+      p.d_acc[t] = dnew;
+      p.tok_action[pos] = skip ? TRIMMOE_ACT_SKIP : TRIMMOE_ACT_EXEC;
+      p.tok_keep[pos] = 1;
+      if (!skip) atomicAdd(&s_xcnt, 1);
+      if (p.tr_action) p.tr_action[t] = skip ? TRIMMOE_ACT_SKIP : TRIMMOE_ACT_EXEC;
+      if (p.tr_importance) p.tr_importance[t] = I;
+      if (p.tr_d_acc) p.tr_d_acc[t] = dnew;
+      if (p.tr_counters) {
+        atomicAdd(&p.tr_counters[0], 1);
+        atomicAdd(&p.tr_counters[skip ? 2 : 1], 1);
+        if (!skip && bns) atomicAdd(&p.tr_counters[4], bns);
+        if (!skip && n_rem - bns) atomicAdd(&p.tr_counters[5], n_rem - bns);
+        if (n_rem) atomicAdd(&p.tr_counters[8], n_rem);
+      }
+    }
+  } else {
   const int i = threadIdx.x;
   int pos = 0, t = 0, n_loc = 0, n_rem = 0, nsub = 0, nopt = 1;
   float I = 0.f, budget = 0.f, D = 0.f;
-  // each remote slot's candidates: its best substitute at H = 1 (A13), its
-  // C = la_subs least-loss local candidates under look-ahead
-  const int C = LA ? p.la_subs : 1;
-  const int16_t* cand = LA ? la.cand0 : s_subc;
-  const float* candq = LA ? la.candq0 : s_subq;
+  // each remote slot's candidates: its C least-loss local ones
+  const int C = p.la_subs;
+  const int16_t* cand = la.cand0;
+  const float* candq = la.candq0;
   if (i < nt) {
     pos = base + i;
     t = t_pre;
@@ -670,7 +918,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
     sNsub[i] = nsub;
   }
 
-  if constexpr (LA) {
+  {
     // Eq. (39)-(40): cost-to-go of every candidate action of the block's
     // tokens.  Options 0 .. nopt - 1 execute (la_option's mixed-radix
     // numbering over the substitutable remote slots); option nopt skips.
@@ -739,7 +987,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
 
   if (i < nt) {
     const float wt = p.omega_t, wd = 1.f - p.omega_t;
-    const float* phi = LA ? la.phi + i * la_opt_max(C, k) : nullptr;
+    const float* phi = la.phi + i * la_opt_max(C, k);
     // Eq. (34) + Eq. (31): every way of serving the remote slots (target or
     // a candidate) within the budget
     bool have = false, all_local = false;
@@ -753,7 +1001,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
       if (ns == n_rem) all_local = true;
       float f = wt * ((float)(n_loc + ns) * p.t_local + (float)(n_rem - ns) * p.t_remote) +
                 (budget > 0.f ? wd * sq / budget : 0.f);
-      if constexpr (LA) f += phi[o];  // Eq. (40): per-step cost + cost-to-go
+      f += phi[o];  // Eq. (40): per-step cost + cost-to-go
       const bool better =
           !have || f < bf ||
           (f == bf && (ns < bns || (ns == bns && (mask < bmask || (mask == bmask && o < bo)))));
@@ -772,7 +1020,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
     bool skip = false;
     if (!all_local && I <= p.theta && D + lam <= budget) {
       float fs = budget > 0.f ? wd * lam / budget : 0.f;
-      if constexpr (LA) fs += phi[nopt];
+      fs += phi[nopt];
       skip = fs < bf;
     }
     if (!have) skip = false;  // unreachable: the empty assignment is feasible
@@ -829,6 +1077,7 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
       if (nremote) atomicAdd(&p.tr_counters[5], nremote);
       if (nroute_remote) atomicAdd(&p.tr_counters[8], nroute_remote);
     }
+  }
   }
   __syncthreads();
   for (int e = threadIdx.x; e < E; e += blockDim.x) p.blk_cnt[(size_t)blockIdx.x * E + e] = s_cnt[e];
@@ -958,10 +1207,6 @@ __global__ __launch_bounds__(1024) void k_scan(LayerParams p) {
 }
 
 // ------------------------------------------------- stable row permutation --
-// bounds of the fused scan: block histogram entries (route blocks x experts)
-// and route blocks a bucket block holds in LDS
-constexpr int kFusedScanEntries = 4096;
-constexpr int kFusedScanBlocks = 1024;
 // Row of (active position pos, merged row j with expert e) =
 //   exp_off[e] + (rows of e in earlier blocks) + (rows of e earlier in block),
 // i.e. rows of one expert stay in token order.  No hidden state is copied:
@@ -1264,7 +1509,6 @@ __global__ __launch_bounds__(1024) void k_compact(LayerParams p) {
 }
 
 // -------------------------------------------------------------- launchers --
-static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 hipError_t launch_state_reset(const trimmoe_model* m, const trimmoe_state* s, hipStream_t st) {
   const int T = s->n_tokens;
@@ -1280,28 +1524,37 @@ hipError_t launch_trace_fill(const LayerParams& p, int n_layers, hipStream_t st)
 }
 
 size_t route_lds_bytes(bool bf16, int E, int d, int horizon, int trans_b, int k, int la_subs) {
-  size_t lds = (size_t)(bf16 ? route_ks(E, d) : 1) * RB * E * sizeof(float);
+  // K splits of the logits that the limit on the look-ahead tables counts
+  int ks = 1;
+  if (bf16) {
+    const int nct = (E + 15) / 16;
+    while (nct * ks < kRouteWaves) ks *= 2;
+    while (ks > 1 && d % (32 * ks) != 0) ks /= 2;
+  }
+  size_t lds = (size_t)ks * RB * E * sizeof(float);
   if (horizon > 1) lds += la_carve(nullptr, E, trans_b, k, horizon - 1, la_subs, nullptr);
   return lds;
 }
 
 hipError_t launch_route(const LayerParams& p, bool bf16, hipStream_t st) {
   const int nb = cdiv(p.T, p.rb);
-  const size_t lds = route_lds_bytes(bf16, p.E, p.d, p.horizon, p.trans_b, p.k, p.la_subs);
+  const size_t zs = (size_t)RB * p.E * sizeof(float), parts = zs * logit_splits(p.E);
   const dim3 grid(nb), block(64 * kRouteWaves);
   if (p.horizon > 1) {
+    // logits and tables, or before those the partial sums and their ring: the
+    // first is within route_lds_bytes, which validation limits, the second
+    // under 120 KB for any E
+    const size_t tables = zs + la_carve(nullptr, p.E, p.trans_b, p.k, p.horizon - 1, p.la_subs, nullptr);
+    const size_t lds = tables > parts + kLogitRing ? tables : parts + kLogitRing;
     auto kern = bf16 ? k_route<true, true> : k_route<false, true>;
-    if (lds > 65536) {
-      const hipError_t e =
-          hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-      if (e != hipSuccess) return e;
-    }
+    const hipError_t e = hipFuncSetAttribute(
+        (const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, st, p);
   } else if (bf16) {
-    hipLaunchKernelGGL((k_route<true, false>), grid, block, lds, st, p);
+    hipLaunchKernelGGL((k_route<true, false>), grid, block, parts, st, p);
   } else {
-    hipLaunchKernelGGL((k_route<false, false>), grid, block, lds, st, p);
+    hipLaunchKernelGGL((k_route<false, false>), grid, block, parts, st, p);
   }
   return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-// Arguments and lane helpers shared by the bf16 matrix kernels (gemm.hip,
-// skinny.hip).  Not part of the public ABI.
+// Arguments and lane helpers shared by the matrix kernels (gemm.hip, skinny.hip)
+// and the routing (decide.hip).  Not part of the public ABI.
 #pragma once
 
 #include "common.h"
@@ -10,6 +10,12 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+typedef __attribute__((address_space(3))) char lds_byte;
+
+// 16-byte chunk c of row r sits at chunk c ^ swz16(r) of its LDS row, so that
+// the 16 rows of a fragment read spread over the banks
+__device__ __forceinline__ int swz16(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 // barrier for plain LDS traffic that leaves vector-memory operations in flight
 __device__ __forceinline__ void lds_barrier() {

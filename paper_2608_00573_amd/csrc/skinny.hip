@@ -50,11 +50,6 @@ constexpr int LDS = RING + RED;
 constexpr int KSTEP = 32;                        // K of one MFMA
 }  // namespace skinny
 
-// 16-byte chunk c of row r sits at chunk c ^ swz16(r) of its LDS row, so that
-// the 16 rows of a fragment read spread over the banks
-__device__ __forceinline__ int swz16(int r) { return (r & 7) ^ ((r >> 3) & 1); }
-
-typedef __attribute__((address_space(3))) char lds_byte;
 __device__ __forceinline__ uint32_t lds_offset(const char* p) {
   return (uint32_t)(uintptr_t)(const lds_byte*)(p);
 }

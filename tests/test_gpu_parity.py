@@ -101,6 +101,26 @@ def test_decode_sized_relu_top1_ragged_up():
     _run_and_compare(cfg)
 
 
+@pytest.mark.parametrize("dtype,E,k,d,T", [
+    ("bf16", 16, 8, 64, 9),       # one column tile; K of one slice; every slot count
+    ("bf16", 17, 2, 832, 300),    # two column tiles; a partial last slice
+    ("bf16", 48, 5, 576, 40),     # three column tiles, two of the eight wavefronts idle
+    ("bf16", 65, 4, 192, 700),    # five column tiles; 16-token blocks
+    ("bf16", 129, 3, 128, 33),    # nine column tiles: a wavefront takes two
+    ("f32", 8, 2, 528, 5000),     # fp32 steps of 16 K; 32-token blocks
+    ("f32", 33, 4, 72, 20),       # fp32 rows of a partial step: FMA logits
+    ("f32", 256, 8, 64, 50),      # the most experts and slots
+])
+def test_route_blocks(dtype, E, k, d, T):
+    # router logits through the LDS ring, top-k, and the register form of the
+    # decision, at the edges of their tiles and loops
+    cfg = workload("tiny_fp32", dtype=dtype, n_experts=E, n_local=max(1, E // 2), top_k=k,
+                   d_model=d, d_ff=64, n_tokens=T, vocab_exit=200, n_layers=2,
+                   normalize_topk=1, budget=0.05)
+    _, _, gtr, _, _, _ = _run_and_compare(cfg)
+    assert (gtr["kind"] == O.KIND_SUB).any()
+
+
 @pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
     ("swiglu", 1, 1, 1, 64, 64, 0, 1000),       # K of two k-steps: half the wavefronts idle
     ("relu", 16, 1, 2, 128, 192, 64, 17),       # one full 16-row tile; one row past a group
