@@ -242,22 +242,49 @@ struct LaView {
   float wt, wd, tl, tr;
 };
 
-// next-layer tuple `it` of sources x out of level j: targets and probability
-// (slot 0 is the most significant digit; padding entries give 0)
-__device__ inline float la_tuple(const LaView& v, int j, const int* x, int it, int* tau) {
-  const int16_t* to = v.tto + (size_t)j * v.E * v.B;
-  const float* pr = v.tp + (size_t)j * v.E * v.B;
-  int div = v.ntup;
-  float prob = 1.f;
-  for (int s = 0; s < v.k; ++s) {
-    div /= v.B;
-    const int dgt = (it / div) % v.B;
-    const int t = to[x[s] * v.B + dgt];
-    tau[s] = t < 0 ? 0 : t;
-    prob = t < 0 ? 0.f : prob * pr[x[s] * v.B + dgt];
+// Next-layer tuples of sources x out of level j in index order (slot 0 is the
+// most significant digit): targets and probability of each (padding entries
+// give 0).  The digits count up instead of being divided out of the index.
+struct LaTuples {
+  int dgt[TRIMMOE_MAX_LOOKAHEAD_TOPK];
+  __device__ __forceinline__ void first() {
+#pragma unroll
+    for (int s = 0; s < TRIMMOE_MAX_LOOKAHEAD_TOPK; ++s) dgt[s] = 0;
   }
-  return prob;
-}
+  __device__ __forceinline__ void at(int it, int k, int B) {
+#pragma unroll
+    for (int s = TRIMMOE_MAX_LOOKAHEAD_TOPK - 1; s >= 0; --s) {
+      dgt[s] = 0;
+      if (s < k) {
+        dgt[s] = it % B;
+        it /= B;
+      }
+    }
+  }
+  __device__ __forceinline__ void next(int k, int B) {
+    bool carry = true;
+#pragma unroll
+    for (int s = TRIMMOE_MAX_LOOKAHEAD_TOPK - 1; s >= 0; --s)
+      if (s < k && carry) {
+        carry = ++dgt[s] == B;
+        if (carry) dgt[s] = 0;
+      }
+  }
+  __device__ __forceinline__ float get(const LaView& v, int j, const int* x, int* tau) const {
+    const int16_t* to = v.tto + (size_t)j * v.E * v.B;
+    const float* pr = v.tp + (size_t)j * v.E * v.B;
+    float prob = 1.f;
+#pragma unroll
+    for (int s = 0; s < TRIMMOE_MAX_LOOKAHEAD_TOPK; ++s)
+      if (s < v.k) {
+        const int at = x[s] * v.B + dgt[s];
+        const int t = to[at];
+        tau[s] = t < 0 ? 0 : t;
+        prob = t < 0 ? 0.f : prob * pr[at];
+      }
+    return prob;
+  }
+};
 
 // candidates of a row of C entries (-1 padded, ascending Q) that fit the
 // budget on their own: D + Q <= b.  An option using any other one is
@@ -281,8 +308,12 @@ __device__ inline float la_option(int o, int k, const int* tau, const int* rs, c
   float sq = 0.f;
   int m = 0;
   for (int u = 0; u < nsub; ++u) {
-    const int d = o % rad[u];
-    o /= rad[u];
+    // o / rad by a 16-bit reciprocal, exact for the options there can be (o
+    // under 1024, rad 2 .. 1 + TRIMMOE_MAX_LA_SUBS)
+    const int r = rad[u];
+    const int od = (o * (r == 2 ? 32768 : r == 3 ? 21846 : r == 4 ? 16384 : 13108)) >> 16;
+    const int d = o - od * r;
+    o = od;
     if (d > 0) {
       const int s = rs[u];
       const size_t at = (size_t)tau[s] * C + d - 1;
@@ -298,17 +329,77 @@ __device__ inline float la_option(int o, int k, const int* tau, const int* rs, c
 template <int R>
 __device__ float la_phi(const LaView& v, int j, const int* x, float D, float I, float b);
 
+// The last level of the horizon: nothing depends on which expert runs, only on
+// what is charged, and sums and quotients of larger charges are not smaller.
+// So among the options that substitute the same slots the one with every
+// slot's least-loss candidate costs least and is feasible if any is: 2^n
+// options instead of (1 + C)^n, same least cost.  With the division-free
+// numbering and the lanes shared out over options (below), the routing kernel
+// of a 32-token decode batch at H = 3 (top-2, B = 4, C = 4) takes 55 us instead
+// of 264.
+__device__ __forceinline__ float la_last(const LaView& v, int j, const int* tau, float D, float I,
+                                         float b) {
+  const int lev = j - 1;
+  const uint8_t* mask = v.mask + (size_t)lev * v.E;
+  const int16_t* cand = v.cand + (size_t)lev * v.E * v.C;
+  const float* candq = v.candq + (size_t)lev * v.E * v.C;
+  float q[TRIMMOE_MAX_LOOKAHEAD_TOPK];
+  int n_loc = 0;
+  unsigned can = 0;
+#pragma unroll
+  for (int s = 0; s < TRIMMOE_MAX_LOOKAHEAD_TOPK; ++s) {
+    q[s] = 0.f;
+    if (s < v.k) {
+      const int e = tau[s];
+      const bool local = mask[e], have = cand[e * v.C] >= 0;
+      q[s] = candq[e * v.C];
+      if (local)
+        ++n_loc;
+      else if (have && D + q[s] <= b)
+        can |= 1u << s;
+    }
+  }
+  const int n_rem = v.k - n_loc;
+  float best = __builtin_inff();
+  bool all_local = false;
+  unsigned m = 0;
+  for (;;) {
+    float sq = 0.f;
+#pragma unroll
+    for (int s = 0; s < TRIMMOE_MAX_LOOKAHEAD_TOPK; ++s)
+      if ((m >> s) & 1) sq += q[s];
+    if (D + sq <= b) {
+      const int ns = __popc(m);
+      if (ns == n_rem) all_local = true;
+      // (the quotient of a zero charge is zero)
+      best = fminf(best, v.wt * ((float)(n_loc + ns) * v.tl + (float)(n_rem - ns) * v.tr) +
+                             (b > 0.f && m ? v.wd * sq / b : 0.f));
+    }
+    m = (m - can) & can;
+    if (m == 0) break;
+  }
+  if (!all_local) {
+    const float lam = fminf(1.f, v.slope[lev] * I);
+    if (I <= v.theta[lev] && D + lam <= b) best = fminf(best, b > 0.f ? v.wd * lam / b : 0.f);
+  }
+  return best;
+}
+
 // least per-step cost plus cost-to-go (R more levels) of the options at
 // level j for routed targets tau with D-hat = D: the rule of Eq. (31),
-// (32), (34), (35) and the importance admission at layer + j
+// (32), (34), (35) and the importance admission at layer + j.  Lane g of G
+// takes every G-th option (the skip is the last); the least over the lanes is
+// the value.
 template <int R>
-__device__ float la_inner(const LaView& v, int j, const int* tau, float D, float I, float b) {
+__device__ float la_inner(const LaView& v, int j, const int* tau, float D, float I, float b, int g,
+                          int G) {
   const int lev = j - 1;
   const uint8_t* mask = v.mask + (size_t)lev * v.E;
   const int16_t* cand = v.cand + (size_t)lev * v.E * v.C;
   const float* candq = v.candq + (size_t)lev * v.E * v.C;
   int n_loc = 0, n_rem = 0, nsub = 0, nopt = 1;
   int rs[TRIMMOE_MAX_LOOKAHEAD_TOPK], rad[TRIMMOE_MAX_LOOKAHEAD_TOPK];
+  float sq_all = 0.f;  // every slot's least-loss candidate
   for (int s = 0; s < v.k; ++s) {
     const int e = tau[s];
     if (mask[e]) {
@@ -320,53 +411,69 @@ __device__ float la_inner(const LaView& v, int j, const int* tau, float D, float
         rs[nsub] = s;
         rad[nsub++] = 1 + n;
         nopt *= 1 + n;
+        sq_all += candq[(size_t)e * v.C];
       }
     }
   }
+  // a feasible all-local option exists iff that one is feasible (Eq. (35))
+  const bool all_local = nsub == n_rem && D + sq_all <= b;
+  const float lam = fminf(1.f, v.slope[lev] * I);
+  const bool skip = !all_local && I <= v.theta[lev] && D + lam <= b;
   float best = __builtin_inff();
-  bool all_local = false;
-  for (int o = 0; o < nopt; ++o) {
-    int x[TRIMMOE_MAX_LOOKAHEAD_TOPK], m;
-    const float sq = la_option(o, v.k, tau, rs, rad, nsub, cand, candq, v.C, x, &m);
-    if (D + sq <= b) {
+  for (int o = g; o < nopt + (skip ? 1 : 0); o += G) {
+    int x[TRIMMOE_MAX_LOOKAHEAD_TOPK], m = 0;
+    float charge, f;
+    if (o < nopt) {
+      charge = la_option(o, v.k, tau, rs, rad, nsub, cand, candq, v.C, x, &m);
+      if (!(D + charge <= b)) continue;
       const int ns = __popc(m);
-      if (ns == n_rem) all_local = true;
-      float f = v.wt * ((float)(n_loc + ns) * v.tl + (float)(n_rem - ns) * v.tr) +
-                (b > 0.f ? v.wd * sq / b : 0.f);
-      if constexpr (R > 0) f += la_phi<R>(v, j, x, D + sq, I, b);
-      best = fminf(best, f);
+      f = v.wt * ((float)(n_loc + ns) * v.tl + (float)(n_rem - ns) * v.tr) +
+          (b > 0.f ? v.wd * charge / b : 0.f);
+    } else {
+      for (int s = 0; s < v.k; ++s) x[s] = tau[s];
+      charge = lam;
+      f = b > 0.f ? v.wd * lam / b : 0.f;
     }
-  }
-  if (!all_local) {
-    const float lam = fminf(1.f, v.slope[lev] * I);
-    if (I <= v.theta[lev] && D + lam <= b) {
-      float f = b > 0.f ? v.wd * lam / b : 0.f;
-      if constexpr (R > 0) f += la_phi<R>(v, j, tau, D + lam, I, b);
-      best = fminf(best, f);
-    }
+    best = fminf(best, f + la_phi<R>(v, j, x, D + charge, I, b));
   }
   return best;
 }
 
-// Phi^(R): expectation over the next layer's tuples of la_inner<R - 1>
+// Phi^(R): expectation over the next layer's tuples of the level after j
 template <int R>
 __device__ float la_phi(const LaView& v, int j, const int* x, float D, float I, float b) {
   float acc = 0.f;
-  for (int it = 0; it < v.ntup; ++it) {
+  LaTuples tuples;
+  tuples.first();
+  for (int it = 0; it < v.ntup; ++it, tuples.next(v.k, v.B)) {
     int tau[TRIMMOE_MAX_LOOKAHEAD_TOPK];
-    const float prob = la_tuple(v, j, x, it, tau);
-    if (prob != 0.f) acc += prob * la_inner<R - 1>(v, j + 1, tau, D, I, b);
+    const float prob = tuples.get(v, j, x, tau);
+    if (prob != 0.f) {
+      if constexpr (R == 1)
+        acc += prob * la_last(v, j + 1, tau, D, I, b);
+      else
+        acc += prob * la_inner<R - 1>(v, j + 1, tau, D, I, b, 0, 1);
+    }
   }
   return acc;
 }
 
-// la_inner at level 1 with `rem` further levels (horizon - 2)
+// the level after the decision's with `rem` further levels (horizon - 2): lane
+// g's share of G
 __device__ inline float la_inner_top(const LaView& v, int rem, const int* tau, float D, float I,
-                                     float b) {
-  if (rem == 0) return la_inner<0>(v, 1, tau, D, I, b);
-  if (rem == 1) return la_inner<1>(v, 1, tau, D, I, b);
-  return la_inner<2>(v, 1, tau, D, I, b);
+                                     float b, int g, int G) {
+  if (rem == 0) return la_last(v, 1, tau, D, I, b);
+  if (rem == 1) return la_inner<1>(v, 1, tau, D, I, b, g, G);
+  return la_inner<2>(v, 1, tau, D, I, b, g, G);
 }
+
+struct MinStep {
+  float& v;
+  template <int OFF>
+  __device__ __forceinline__ void run() {
+    v = fminf(v, group_other<OFF>(v));
+  }
+};
 
 // options of a token at the layer itself: (1 + C)^k execute options at most,
 // plus the skip
@@ -950,7 +1057,11 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
     for (int r = 0; r * tpr < p.rb; ++r) {
       const int ti = slot + tpr * r;
       const int nall = ti < nt ? la.nopt[ti] + 1 : 0;  // with the skip
-      for (int it = wsub * 64 + lane; it < nall * ntup; it += wpt * 64) {
+      // G lanes per branch share the options of the level after it (their
+      // number varies from 1 to (1 + C)^k + 1 between branches; one lane each
+      // left a wavefront waiting for its longest branch)
+      const int G = rem > 0 ? 8 : 1, g = lane & (G - 1);
+      for (int it = (wsub * 64 + lane) / G; it < nall * ntup; it += wpt * 64 / G) {
         const int o = it / ntup, tup = it % ntup;
         const float Dt = la.tokD[ti], bt = la.tokB[ti], It = la.tokI[ti];
         int x[TRIMMOE_MAX_LOOKAHEAD_TOPK];
@@ -969,10 +1080,16 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
         float val = 0.f;
         if (feasible) {
           int tau[TRIMMOE_MAX_LOOKAHEAD_TOPK];
-          const float prob = la_tuple(lv, 0, x, tup, tau);
-          if (prob != 0.f) val = prob * la_inner_top(lv, rem, tau, Dt + charge, It, bt);
+          LaTuples tuples;
+          tuples.at(tup, k, lv.B);
+          const float prob = tuples.get(lv, 0, x, tau);
+          if (prob != 0.f) {
+            float least = la_inner_top(lv, rem, tau, Dt + charge, It, bt, g, G);
+            group_steps(G, MinStep{least});
+            val = prob * least;
+          }
         }
-        br[it] = val;
+        if (g == 0) br[it] = val;
       }
       __syncthreads();
       if (wsub == 0)
