@@ -34,6 +34,7 @@ KERNELS = {
     "k_ffn_big<1>": "_ZN7trimmoe9k_ffn_bigILi1EEEvNS_7FfnArgsE",
     "k_ffn_big<2>": "_ZN7trimmoe9k_ffn_bigILi2EEEvNS_7FfnArgsE",
     "k_exit_big": "_ZN7trimmoe10k_exit_bigENS_8ExitArgsE",
+    "k_argmax_big": "_ZN7trimmoe12k_argmax_bigENS_8ExitArgsE",
 }
 WAIT_STATES = 19
 

@@ -32,6 +32,7 @@ def _mat(seed, tid, shape, sigma, dtype):
     (torch.bfloat16, 20, 2112, 17),       # ... two row tiles, one block
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles, ragged vocabulary
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
+    (torch.bfloat16, 700, 2048, 1030),    # large-group tiles, ragged rows and vocabulary
 ])
 def test_head_argmax_matches_oracle(dtype, V, d, Q):
     log(f"[exit-head] argmax {dtype} V={V} d={d} Q={Q}")
