@@ -187,10 +187,9 @@ size_t carve(const trimmoe_model* m, int T, char* base, LayerParams* p) {
   P.sk_part = big_any ? (float*)take((size_t)kSkSlots * 256 * 256 * 4) : nullptr;
   P.row_src = (int32_t*)take(R * 4);
   P.act_buf = take(R * F * es);
-  const int splits = bf16 ? down_splits(max_tiles, d, F) : 1;
-  P.y_buf = (float*)take(down_slice_rows_max(m, Tm) * d * 4);
-  P.y_split_stride = R * d;
-  P.down_splits = splits;
+  const size_t y_rows = down_slice_rows_max(m, Tm);
+  P.y_buf = (float*)take(y_rows * d * 4);
+  P.y_cap_rows = (long long)y_rows;
   P.act_s = Fs ? take((size_t)Tm * Fs * es) : nullptr;
   P.y_s = Fs ? (float*)take((size_t)Tm * d * 4) : nullptr;
   P.hx = take((size_t)Tm * d * es);
@@ -243,16 +242,15 @@ void fill_params(LayerParams& P, const trimmoe_model* m, int l, const trimmoe_po
   P.trans_b = m->trans_b;
   P.rb = route_block_tokens(T, P.horizon > 1, m->n_experts);
   P.bm = expert_tile_rows(m->dtype == TRIMMOE_BF16, T, k, m->n_experts, m->d_model, m->d_ff);
-  // the large-group down GEMM cuts the tiles of its last round along K
-  // instead of splitting every tile
-  if (P.bm == kBigBM) {
-    P.down_splits = 1;
-  } else {
+  // the large-group down GEMM cuts the tiles of its last round along K instead
+  // of splitting every tile; the weight-streaming one splits K in the block,
+  // and fp32 tiles do not split it
+  const bool big = P.bm == kBigBM;
+  if (big || m->dtype != TRIMMOE_BF16 || T <= kSkinnyTokens) P.y_cap_rows = 0;
+  if (!big) {
     P.sk_flag = nullptr;
     P.sk_part = nullptr;
   }
-  // the weight-streaming down GEMM sums its K split in the block
-  if (T <= kSkinnyTokens) P.down_splits = 1;
   for (int j = 0; j < kMaxLookahead; ++j) {
     const bool later = j + 1 < P.horizon;  // layer l + j + 1 is looked at
     const trimmoe_layer* Lj = later ? &m->layers[l + j + 1] : nullptr;

@@ -86,6 +86,29 @@ inline bool big_exit(bool bf16, int T, int V, int d) {
 constexpr int kWideTokens = 4096;
 constexpr int kGemmBN = 128;
 constexpr int kGemmBK = 64;
+// K splits of the routed down GEMM (128-row tiles), from the live tile and row
+// counts: the row tiles of an uneven batch are fewer than the bound the host
+// knows (one per expert more than the rows need), and too few tiles leave CUs
+// idle.  The fewest K slices on the busiest of n_cu CUs, 1, 2, 4 or 8 splits
+// of at least 8 slices whose partial rows the workspace holds; a split has to
+// save an eighth (its partials are written, and read by the combine, once
+// more).  The GEMM and the combine evaluate the same rule.  Mixtral shapes, 333
+// tokens (7 row tiles where the bound is 14): down 225 -> 140 us.
+__host__ __device__ inline int live_down_splits(int n_mt, int rows, int N, int K, long long cap_rows,
+                                                int n_cu) {
+  const int tiles = n_mt * ((N + 255) / 256), nk = K / kGemmBK;
+  int best = 1;
+  long long best_cost = (long long)((tiles + n_cu - 1) / n_cu) * nk;
+  for (int s = 2; s <= 8; s *= 2) {
+    if (nk % s != 0 || nk / s < 8 || (long long)rows * s > cap_rows) break;
+    const long long cost = (long long)((tiles * s + n_cu - 1) / n_cu) * (nk / s);
+    if (8 * cost <= 7 * best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
 // bf16 batches of up to this many tokens run the weight-streaming kernels
 // (skinny.hip) for every GEMM
 constexpr int kSkinnyTokens = 64;
@@ -242,9 +265,9 @@ struct LayerParams {
   float* sk_part;      // [kSkSlots][256][256] compact partials of later pieces
   int32_t* row_src;    // [T*k] token whose h row feeds each permuted row
   void* act_buf;       // [T*k, F]
-  float* y_buf;        // [down_splits][T*k, d] partial down-projection slices
-  size_t y_split_stride;  // elements between slices of y_buf
-  int down_splits;     // K splits of the routed down GEMM (bf16 path)
+  float* y_buf;        // [splits][rows, d] partial down-projection slices
+  long long y_cap_rows;  // rows y_buf holds when the down GEMM splits K
+                         // (live_down_splits), or 0: one slice
   void* act_s;         // [T, Fs]
   float* y_s;          // [T, d]
   void* hx;            // [T, d]    updated rows of executed tokens (exit input;

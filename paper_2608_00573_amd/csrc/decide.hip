@@ -1472,6 +1472,14 @@ __global__ __launch_bounds__(256) void k_combine(LayerParams p) {
   const int per_tok = p.d / 8;
   const size_t total = (size_t)n_x * per_tok;
   ST* h = static_cast<ST*>(p.h);
+  // the down GEMM's K split slices
+  int splits = 1;
+  size_t split_stride = 0;
+  if (p.y_cap_rows > 0) {
+    const int rows = p.counts[kCntRows];
+    splits = live_down_splits(p.counts[kCntTiles], rows, p.d, p.F, p.y_cap_rows, p.n_cu);
+    split_stride = (size_t)rows * p.d;
+  }
   for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (size_t)gridDim.x * blockDim.x) {
     const int j = (int)(idx / per_tok), c = (int)(idx % per_tok) * 8;
@@ -1487,8 +1495,8 @@ __global__ __launch_bounds__(256) void k_combine(LayerParams p) {
       const float w = p.tok_w[(size_t)pos * p.k + s];
       const float4* y = reinterpret_cast<const float4*>(p.y_buf + (size_t)row * p.d + c);
       float4 v0 = y[0], v1 = y[1];
-      for (int q = 1; q < p.down_splits; ++q) {
-        const float4* yq = reinterpret_cast<const float4*>(p.y_buf + q * p.y_split_stride +
+      for (int q = 1; q < splits; ++q) {
+        const float4* yq = reinterpret_cast<const float4*>(p.y_buf + q * split_stride +
                                                            (size_t)row * p.d + c);
         const float4 a0 = yq[0], a1 = yq[1];
         v0.x += a0.x; v0.y += a0.y; v0.z += a0.z; v0.w += a0.w;

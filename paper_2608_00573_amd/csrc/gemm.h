@@ -91,9 +91,9 @@ struct FfnArgs {
   const int4* tiles;      // grouped mode
   const int* n_tiles;     // grouped mode: live tiles (device)
   const int* dense_rows;  // dense mode: live rows (device), else NULL
-  void* out;              // up: bf16 [rows, N]; down: f32 [split][rows_cap, N]
-  size_t split_stride;    // elements between split slices of `out`
-  int n_split;            // K splits (down GEMM); 1 otherwise
+  void* out;              // up: bf16 [rows, N]; down: f32 [split][rows, N]
+  const int* n_rows;      // down GEMM: live rows (device), the rows of a split slice
+  long long cap_rows;     // ... rows `out` holds (live_down_splits), or 0: one slice
   int act;                // up: TRIMMOE_ACT_*
   int* sk_flag;           // large-group down GEMM: per-tile piece words (see SkPlan), or NULL
   float* sk_part;         // ... and the compact partials of pieces 1.. of cut tiles

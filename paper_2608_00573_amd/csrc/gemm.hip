@@ -431,6 +431,7 @@ struct FfnSrc {
   const TileSched& S;
   int dense_m1;  // dense mode: live rows
   int nk;
+  size_t split_stride;  // elements between K split slices of the output
 
   __device__ __forceinline__ Desc desc(int j) const {
     int mt, nt, sp;
@@ -475,7 +476,7 @@ struct FfnSrc {
       asm volatile("" : "+s"(N));  // per-tile value: keeps the offsets below inside the tile loop
       char* out = static_cast<char*>(a.out) + ((size_t)m0 * N + nt) * ES;
       if constexpr (!UP)
-        out += (size_t)__builtin_amdgcn_readfirstlane(d.sp) * a.split_stride * ES;
+        out += (size_t)__builtin_amdgcn_readfirstlane(d.sp) * split_stride * ES;
       const __amdgpu_buffer_rsrc_t ro =
           __builtin_amdgcn_make_buffer_rsrc(out, (short)0, valid * N * ES, 0x00020000);
       const bool odd = lane & 1;
@@ -535,7 +536,7 @@ struct FfnSrc {
             }
             static_cast<float*>(a.out)[o] = v;
           } else {
-            static_cast<float*>(a.out)[d.sp * a.split_stride + o] = acc[i][j][r];
+            static_cast<float*>(a.out)[o] = acc[i][j][r];
           }
         }
       }
@@ -550,10 +551,18 @@ __global__ __launch_bounds__(T::THREADS) void k_ffn_mma(FfnArgs a) {
   const int n_mt = a.dense_rows ? (dense_m1 + T::BM - 1) / T::BM : *a.n_tiles;
   TileSched S;
   int ntiles;
-  if (!S.init(n_mt, n_nt, a.n_split, ntiles)) return;
+  int n_split = 1;
+  size_t split_stride = 0;
+  if constexpr (!UP)
+    if (a.cap_rows > 0) {
+      const int rows = *a.n_rows;
+      n_split = live_down_splits(n_mt, rows, a.N, a.K, a.cap_rows, gridDim.x);
+      split_stride = (size_t)rows * a.N;
+    }
+  if (!S.init(n_mt, n_nt, n_split, ntiles)) return;
   clock_mark(a.clk, true);
-  const int nk = (a.K / BK) / a.n_split;
-  const FfnSrc<T, UP> src{a, S, dense_m1, nk};
+  const int nk = (a.K / BK) / n_split;
+  const FfnSrc<T, UP> src{a, S, dense_m1, nk, split_stride};
   dma_gemm_stream<T>(lds, ntiles, nk, src);
   clock_mark(a.clk, false);
 }
@@ -1040,8 +1049,8 @@ struct SkPlan {
 };
 
 // MODE 0: SwiGLU up and gate (NB operands W0 / W1, 128 output columns per
-// tile), MODE 1: ReLU up, MODE 2: down (fp32 out; K splits, or stream-K
-// pieces when a.sk_flag is set)
+// tile), MODE 1: ReLU up, MODE 2: down (fp32 out; the tiles of the last round
+// cut along K when a.sk_flag is set)
 template <int MODE>
 __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
   constexpr bool DUAL = MODE == 0;
@@ -1071,9 +1080,9 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
   const int cc = 8 * ((tid & 7) ^ swz(r0));
   const __amdgpu_buffer_rsrc_t ra = buf_rsrc(a.X);
   AccBig acc;
-  // output tile (mt, nt) over K slices [ka, ka + nkp) into partial slot sp
-  // of its rows, or (cslot >= 0, down GEMM) compact partial cslot
-  auto piece = [&](int mt, int nt, int ka, int nkp, int sp, int cslot) {
+  // output tile (mt, nt) over K slices [ka, ka + nkp) into its rows, or
+  // (cslot >= 0, down GEMM) compact partial cslot
+  auto piece = [&](int mt, int nt, int ka, int nkp, int cslot) {
     int e = 0, m0, m1;
     if (a.dense_rows) {
       m0 = mt * big::BM;
@@ -1114,8 +1123,8 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
         big_store_partial(a.sk_part + (size_t)cslot * big::BM * big::BN, big::BN, acc, a_valid,
                           b_valid, wm, wn, lane);
       else
-        big_store_partial(static_cast<float*>(a.out) + sp * a.split_stride + (size_t)m0 * a.N + n0,
-                          a.N, acc, a_valid, b_valid, wm, wn, lane);
+        big_store_partial(static_cast<float*>(a.out) + (size_t)m0 * a.N + n0, a.N, acc, a_valid,
+                          b_valid, wm, wn, lane);
     } else {
       big_store_act<MODE>(lds, a, acc, m0, n0, a_valid, b_valid, wm, wn, lane);
     }
@@ -1123,13 +1132,13 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
   if (!sk) {
     TileSched S;
     int ntiles;
-    if (!S.init(n_mt, n_nt, a.n_split, ntiles)) return;
+    if (!S.init(n_mt, n_nt, 1, ntiles)) return;
     clock_mark(a.clk, true);
-    const int nk = (a.K / BK) / a.n_split;
+    const int nk = a.K / BK;
     for (int jt = 0; jt < ntiles; ++jt) {
       int mt, nt, sp;
       S.decode(jt, mt, nt, sp);
-      piece(mt, nt, sp * nk, nk, sp, -1);
+      piece(mt, nt, 0, nk, -1);
     }
     clock_mark(a.clk, false);
     return;
@@ -1144,7 +1153,7 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
     for (int jt = 0; jt < ntiles; ++jt) {
       int mt, nt, sp;
       S.decode(jt, mt, nt, sp);
-      piece(mt, nt, 0, nk, 0, -1);
+      piece(mt, nt, 0, nk, -1);
       if (tid == 0) a.sk_flag[mt * n_nt + nt] = 0;
     }
   }
@@ -1160,7 +1169,7 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
     S.n_nt = n_nt;
     S.decode_abs(plan.dp + t, mt, nt, sp);
     const int base = t * (plan.s - 1);
-    piece(mt, nt, k0, k1 - k0, 0, q == 0 ? -1 : base + q - 1);
+    piece(mt, nt, k0, k1 - k0, q == 0 ? -1 : base + q - 1);
     if (q == 0 && tid == 0) a.sk_flag[mt * n_nt + nt] = (base << 4) | plan.s;
   }
   clock_mark(a.clk, false);
@@ -1759,11 +1768,10 @@ using FfnF32 = Tile<kGemmBM, BN, 1, BN == 128 ? 2 : 4, BN == 128 ? 4 : BN / 32, 
 using ExitF32 = Tile<kExitTileF32Mma, 128, 1, 4, 2, true>;
 using ExitF32Small = Tile<kExitTileF32Mma, 32, 1, 4, 1, true>;
 
-// K splits of the routed down GEMM, only for a tile bound under two tiles
-// per CU (1, 2 or 4, each split keeping at least 8 K slices): the fewest
-// slices on the busiest CU of a 256-CU persistent grid, and on a tie the
-// fewer splits (fewer fp32 partial slices to write and for the combine to
-// read).
+// K splits the workspace provides slice rows for, from the tile bound: under
+// two tiles per CU 1, 2 or 4, each split keeping at least 8 K slices, by the
+// fewest slices on the busiest CU of a 256-CU persistent grid (the launched
+// count follows the live tiles within that room: live_down_splits).
 int down_splits(int max_tiles, int N, int K) {
   constexpr int kCu = 256;
   const int tiles = max_tiles * cdiv(N, DownTile::BN);
@@ -1785,7 +1793,8 @@ int down_splits(int max_tiles, int N, int K) {
 // persistent: at most one block per CU, none beyond the tile bound
 template <class T, bool UP>
 static void launch_ffn_mma(const FfnArgs& a, int max_mt, int n_cu, hipStream_t st) {
-  const dim3 grid(min(max_mt * cdiv(a.N, T::BN) * a.n_split, n_cu));
+  // (a down GEMM that may split K: every CU)
+  const dim3 grid(a.cap_rows > 0 ? n_cu : min(max_mt * cdiv(a.N, T::BN), n_cu));
   hipLaunchKernelGGL((k_ffn_mma<T, UP>), grid, dim3(T::THREADS), 0, st, a);
 }
 
@@ -1794,7 +1803,7 @@ template <int MODE>
 static void launch_ffn_big(const FfnArgs& a, int max_mt, int n_cu, hipStream_t st) {
   const int nt = cdiv(a.N, MODE == 0 ? 128 : big::BN);
   // cut tiles of the down GEMM: up to kSkPieces pieces each
-  const dim3 grid(min(max_mt * nt * (a.sk_flag ? kSkPieces : a.n_split), n_cu));
+  const dim3 grid(min(max_mt * nt * (a.sk_flag ? kSkPieces : 1), n_cu));
   hipLaunchKernelGGL(k_ffn_big<MODE>, grid, dim3(big::THREADS), 0, st, a);
 }
 
@@ -1815,12 +1824,12 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
   const int act = shared ? TRIMMOE_ACT_SWIGLU : p.act;
   if (max_mt <= 0) return hipSuccess;
   if (bf16) {
-    const int n_split = (!up && !shared) ? p.down_splits : 1;
+    const bool split = !up && !shared && p.y_cap_rows > 0;
     // large groups: the routed tile list was built with kBigBM rows per tile
     const bool big = shared ? big_dense(true, p.T, p.d, p.Fs) : p.bm == kBigBM;
     FfnArgs a{static_cast<const bf16_t*>(X), x_idx, static_cast<const bf16_t*>(w0),
               static_cast<const bf16_t*>(w1), w_stride, K, N, p.tiles, &p.counts[kCntTiles],
-              dense, out, p.y_split_stride, n_split, act,
+              dense, out, &p.counts[kCntRows], split ? p.y_cap_rows : 0, act,
               (!up && !shared && big) ? p.sk_flag : nullptr, p.sk_part,
               p.clk ? p.clk + 2 * (shared ? TRIMMOE_CLASS_SHARED
                                           : up ? TRIMMOE_CLASS_UP : TRIMMOE_CLASS_DOWN)
@@ -1843,7 +1852,7 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
   } else if (f32_slices(K)) {
     FfnArgs a{static_cast<const bf16_t*>(X), x_idx, static_cast<const bf16_t*>(w0),
               static_cast<const bf16_t*>(w1), 2 * w_stride, 2 * K, N, p.tiles,
-              &p.counts[kCntTiles], dense, out, p.y_split_stride, 1, act, nullptr, nullptr, nullptr};
+              &p.counts[kCntTiles], dense, out, nullptr, 0, act, nullptr, nullptr, nullptr};
     // the widest tile that still gives every CU one (an fp32 tile is long: 41 us
     // at 128 x 128 x 768)
     const auto fills = [&](int bn) { return max_mt * cdiv(N, bn) >= p.n_cu; };

@@ -157,6 +157,19 @@ def test_fp32_tiles(act, T, k, E, d, F, Fs, V):
     _run_and_compare(cfg)
 
 
+@pytest.mark.parametrize("T,k,E,d,F", [
+    (70, 1, 2, 64, 8192),     # few tiles, long K: eight splits fit the workspace or fewer
+    (130, 2, 8, 320, 1024),   # two splits of eight slices; partial column tiles
+    (400, 1, 3, 128, 1088),   # 17 K slices: no even split
+])
+def test_live_down_splits(T, k, E, d, F):
+    # the down GEMM's K split follows the live tiles; the combine adds the slices
+    cfg = workload("tiny_fp32", dtype="bf16", act="swiglu", n_tokens=T, top_k=k, n_experts=E,
+                   n_local=max(1, E // 2), d_model=d, d_ff=F, vocab_exit=300, n_layers=3,
+                   normalize_topk=1)
+    _run_and_compare(cfg)
+
+
 def test_wide_model_exit_head_ragged():
     # d_model 2048 at 1100 tokens: the exit head takes 256 x 256 tiles with
     # 4 wavefronts; 1100 tokens and 1000 vocabulary rows leave partial token
