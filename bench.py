@@ -131,7 +131,7 @@ def host_cpu():
 def class_kernel(cls, cfg):
     """The library kernel(s) of a kernel class at the workload's batch size,
     by the library's tile selection: grouped GEMMs with at least 1024 rows
-    per expert on average and the shared expert from 2048 tokens run the
+    per expert on average and the shared expert from 4096 tokens run the
     256 x 256 large-group core, the exit head of models with d >= 2048 from
     1024 tokens too; everything else the 8-wavefront streaming core."""
     T, k, E, d = cfg["n_tokens"], cfg["top_k"], cfg["n_experts"], cfg["d_model"]

@@ -58,8 +58,11 @@ constexpr int kBigRowsPerExpert = 1024;
 // kSkPieces runs of K slices, with at most kSkSlots 256 x 256 extra partials
 constexpr int kSkPieces = 8;
 constexpr int kSkSlots = 256;
-// the dense shared-expert GEMMs use the large-group core from this many tokens
-constexpr int kBigDenseTokens = 2048;
+// the dense shared-expert GEMMs use the large-group core from this many tokens:
+// below, its 256-row tiles leave most CUs idle (Qwen shapes, layer step on it
+// and on the 128-row tiles: 2048 tokens 968 and 931 us, 3000 1279 and 1219, 4099
+// 1571 and 1567)
+constexpr int kBigDenseTokens = 4096;
 // the large-group core addresses its operands with 32-bit byte offsets
 inline bool big_offsets_fit(long long rows, long long cols) {
   return rows * cols * 2 < (1ll << 31);
@@ -112,6 +115,11 @@ __host__ __device__ inline int live_down_splits(int n_mt, int rows, int N, int K
 // bf16 batches of up to this many tokens run the weight-streaming kernels
 // (skinny.hip) for every GEMM
 constexpr int kSkinnyTokens = 64;
+// ... and the shared expert, one pass over its weights (which then stay in the
+// last-level cache) per kSkinnyTokens executed tokens, up to this many: two
+// passes (Qwen shapes, layer step: 65 tokens 376 -> 317 us, 150 tokens of which
+// 85 execute 389 -> 340; a third pass costs more than the 128-row tiles)
+constexpr int kSkinnyDenseTokens = 128;
 // vocabulary rows per exit partial (bf16 MFMA tiles / fp32 path).  The
 // weight-streaming exit head writes one partial per block; its workspace is
 // sized for blocks of at least kExitTileBF16Small rows

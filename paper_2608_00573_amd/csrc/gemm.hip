@@ -320,6 +320,22 @@ struct TileSched {
   }
 };
 
+// The tiles from index `from` on as pieces of half their columns: piece q is
+// half q % 2 of tile from + q / 2, and nt counts half-width column tiles
+struct HalfSched {
+  TileSched S;
+  int from;
+  __device__ __forceinline__ bool init(int from_, int n_mt, int n_nt, int& ntiles) {
+    from = from_;
+    return S.init_total(2 * (n_mt * n_nt - from), n_mt, n_nt, ntiles);
+  }
+  __device__ __forceinline__ void decode(int j, int& mt, int& nt, int& sp) const {
+    const int q = S.tb + S.i0 + j * S.bx;
+    S.decode_abs(from + (q >> 1), mt, nt, sp);
+    nt = 2 * nt + (q & 1);
+  }
+};
+
 // A persistent block's GEMM over its ntiles tiles of nk slices each: one
 // continuous stream of K slices through the DMA ring, so the next tile's
 // first slices are in flight while the current tile's epilogue runs.
@@ -418,7 +434,7 @@ __device__ __forceinline__ void dma_gemm_stream(char* lds, int ntiles, int nk, c
 // the expert-sorted rows, or (dense mode, shared expert) cover the first
 // *dense_rows rows.  A rows are gathered through x_idx (the token whose h
 // row feeds each sorted row) when it is set.
-template <class T, bool UP>
+template <class T, bool UP, class Sched = TileSched>
 struct FfnSrc {
   struct Desc {
     int e, m0, m1, nt, sp;
@@ -428,7 +444,7 @@ struct FfnSrc {
     }
   };
   const FfnArgs& a;
-  const TileSched& S;
+  const Sched& S;
   int dense_m1;  // dense mode: live rows
   int nk;
   size_t split_stride;  // elements between K split slices of the output
@@ -543,7 +559,11 @@ struct FfnSrc {
   }
 };
 
-template <class T, bool UP>
+// K from which a last round in halves pays after whole rounds
+constexpr int kHalvesLongK = 2048;
+
+// H: the tile of the last round's halves (up projections), or T
+template <class T, bool UP, class H = T>
 __global__ __launch_bounds__(T::THREADS) void k_ffn_mma(FfnArgs a) {
   __shared__ __align__(16) char lds[DmaTile<T>::LDS];
   const int n_nt = (a.N + T::BN - 1) / T::BN;
@@ -551,6 +571,40 @@ __global__ __launch_bounds__(T::THREADS) void k_ffn_mma(FfnArgs a) {
   const int n_mt = a.dense_rows ? (dense_m1 + T::BM - 1) / T::BM : *a.n_tiles;
   TileSched S;
   int ntiles;
+  if constexpr (H::BN < T::BN) {
+    // A last round that fills at most half the grid runs as twice the tiles of
+    // half the columns.  Those tiles read the A rows twice as often, so whole
+    // rounds keep the wide ones (up/gate in half-width tiles throughout, Mixtral
+    // shapes: 512 tokens +47 us, but 80 tokens -18 us; layer step with halves in
+    // the last round only: 80 tokens 476 -> 451 us, 333: 590 -> 583, 1000:
+    // 1200 -> 1188).  After whole rounds the stream starts again, which a short
+    // K does not win back (Switch shapes, 12 slices, 6000 tokens: 321 -> 324;
+    // less than one round, 65: 78 -> 74).  A column tile cut short has no second
+    // half to give.
+    static_assert(2 * H::BN == T::BN && H::THREADS == T::THREADS, "halves of a tile");
+    static_assert(DmaTile<H>::LDS <= DmaTile<T>::LDS, "the halves use the tile's ring");
+    const int total = n_mt * n_nt, g = gridDim.x, rem = total % g;
+    if (rem > 0 && 2 * rem <= g && a.N % T::BN == 0 && (total < g || a.K >= kHalvesLongK)) {
+      HalfSched Sh;
+      int nhalf;
+      const bool wide = S.init_total(total - rem, n_mt, n_nt, ntiles);
+      const bool half = Sh.init(total - rem, n_mt, n_nt, nhalf);
+      if (!wide && !half) return;
+      clock_mark(a.clk, true);
+      if (wide) {
+        const FfnSrc<T, UP> src{a, S, dense_m1, a.K / BK, 0};
+        dma_gemm_stream<T>(lds, ntiles, a.K / BK, src);
+        // the stream's last DMAs (never read) still land in the ring
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      }
+      if (half) {
+        const FfnSrc<H, UP, HalfSched> src{a, Sh, dense_m1, a.K / BK, 0};
+        dma_gemm_stream<H>(lds, nhalf, a.K / BK, src);
+      }
+      clock_mark(a.clk, false);
+      return;
+    }
+  }
   int n_split = 1;
   size_t split_stride = 0;
   if constexpr (!UP)
@@ -565,6 +619,40 @@ __global__ __launch_bounds__(T::THREADS) void k_ffn_mma(FfnArgs a) {
   const FfnSrc<T, UP> src{a, S, dense_m1, nk, split_stride};
   dma_gemm_stream<T>(lds, ntiles, nk, src);
   clock_mark(a.clk, false);
+}
+
+template <class T>
+__device__ __forceinline__ void dense_down_tiles(const FfnArgs& a, char* lds, int n_mt, int m1) {
+  TileSched S;
+  int ntiles;
+  if (!S.init(n_mt, (a.N + T::BN - 1) / T::BN, 1, ntiles)) return;
+  clock_mark(a.clk, true);
+  const FfnSrc<T, false> src{a, S, m1, a.K / BK, 0};
+  dma_gemm_stream<T>(lds, ntiles, a.K / BK, src);
+  clock_mark(a.clk, false);
+}
+
+// The shared expert's down projection: few row tiles, and the longest K of a
+// layer.  One round of the grid in the narrowest tiles of 64, 128 or 256
+// columns that fit it (a narrower tile is a shorter chain: 128 x 256 x 5632
+// takes 75 us on one CU however many idle beside it), whole wide tiles beyond.
+// Qwen shapes, layer step in 64 / 128 / 256 columns: 300 tokens (2 row tiles)
+// 373 / 382 / 404 us, 1500 (7) 811 / 815 / 837, 2048 (9) 947 / 931 / 946,
+// 3000 (13) 1250 / 1219 / 1237, 6000 (26) 2234 / 2176 / 2163.
+template <class W, class M, class N>
+__global__ __launch_bounds__(W::THREADS) void k_ffn_dense_down(FfnArgs a) {
+  static_assert(W::BM == M::BM && W::BM == N::BM && W::THREADS == M::THREADS &&
+                W::THREADS == N::THREADS, "one block shape");
+  constexpr int L0 = DmaTile<W>::LDS, L1 = DmaTile<M>::LDS, L2 = DmaTile<N>::LDS;
+  __shared__ __align__(16) char lds[L0 > L1 ? (L0 > L2 ? L0 : L2) : (L1 > L2 ? L1 : L2)];
+  const int m1 = *a.dense_rows, n_mt = (m1 + W::BM - 1) / W::BM;
+  const int g = gridDim.x;
+  if (n_mt * ((a.N + N::BN - 1) / N::BN) <= g)
+    dense_down_tiles<N>(a, lds, n_mt, m1);
+  else if (n_mt * ((a.N + M::BN - 1) / M::BN) <= g)
+    dense_down_tiles<M>(a, lds, n_mt, m1);
+  else
+    dense_down_tiles<W>(a, lds, n_mt, m1);
 }
 
 // ------------------------------------------ large-group expert GEMMs --
@@ -1757,6 +1845,11 @@ __global__ __launch_bounds__(256) void k_exit_f32(const float* W, const float* H
 using UpDualTile = Tile<kGemmBM, 128, 2, 2, 4>;  // SwiGLU: up and gate share A
 using UpTile = Tile<kGemmBM, 256, 1, 2, 4>;      // ReLU
 using DownTile = Tile<kGemmBM, 256, 1, 2, 4>;
+// halves of the up tiles, and narrower down tiles of the shared expert
+using UpDualHalf = Tile<kGemmBM, 64, 2, 4, 2>;
+using UpHalf = Tile<kGemmBM, 128, 1, 2, 4>;
+using DownTile128 = Tile<kGemmBM, 128, 1, 2, 4>;
+using DownTile64 = Tile<kGemmBM, 64, 1, 4, 2>;
 
 // fp32: two operands of 64 columns or one of 128 per 8 wavefronts, narrower
 // ones for small problems (4 wavefronts at 32 columns)
@@ -1791,11 +1884,23 @@ int down_splits(int max_tiles, int N, int K) {
 }
 
 // persistent: at most one block per CU, none beyond the tile bound
-template <class T, bool UP>
+template <class T, bool UP, class H = T>
 static void launch_ffn_mma(const FfnArgs& a, int max_mt, int n_cu, hipStream_t st) {
   // (a down GEMM that may split K: every CU)
-  const dim3 grid(a.cap_rows > 0 ? n_cu : min(max_mt * cdiv(a.N, T::BN), n_cu));
-  hipLaunchKernelGGL((k_ffn_mma<T, UP>), grid, dim3(T::THREADS), 0, st, a);
+  const dim3 grid(a.cap_rows > 0 ? n_cu : min(max_mt * cdiv(a.N, H::BN), n_cu));
+  hipLaunchKernelGGL((k_ffn_mma<T, UP, H>), grid, dim3(T::THREADS), 0, st, a);
+}
+
+// an up GEMM; row_tiles: the row tiles of its rows without one more per expert.
+// A short K halves no more than a batch of under half a round (k_ffn_mma), and
+// larger ones keep the kernel without halves (Switch shapes, layer step, 3000 to
+// 8000 tokens: with them 1-2% slower)
+template <class T, class H>
+static void launch_ffn_up(const FfnArgs& a, int max_mt, int row_tiles, int n_cu, hipStream_t st) {
+  if (a.K >= kHalvesLongK || 2 * row_tiles * cdiv(a.N, T::BN) <= n_cu)
+    launch_ffn_mma<T, true, H>(a, max_mt, n_cu, st);
+  else
+    launch_ffn_mma<T, true>(a, max_mt, n_cu, st);
 }
 
 // persistent: at most one block per CU, none beyond the tile bound
@@ -1821,6 +1926,7 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
   void* out = up ? (shared ? p.act_s : p.act_buf) : (shared ? (void*)p.y_s : (void*)p.y_buf);
   const int* dense = shared ? &p.counts[kCntExec] : nullptr;
   const int max_mt = shared ? cdiv(p.T, kGemmBM) : p.max_tiles;
+  const int row_tiles = cdiv(shared ? p.T : p.T * p.k, kGemmBM);
   const int act = shared ? TRIMMOE_ACT_SWIGLU : p.act;
   if (max_mt <= 0) return hipSuccess;
   if (bf16) {
@@ -1834,7 +1940,8 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
               p.clk ? p.clk + 2 * (shared ? TRIMMOE_CLASS_SHARED
                                           : up ? TRIMMOE_CLASS_UP : TRIMMOE_CLASS_DOWN)
                     : nullptr};
-    if (p.T <= kSkinnyTokens) return launch_ffn_skinny(a, up, dual, p.n_cu, st);
+    if (p.T <= (shared ? kSkinnyDenseTokens : kSkinnyTokens))
+      return launch_ffn_skinny(a, up, dual, p.n_cu, st);
     if (big) {
       const int big_mt = shared ? cdiv(p.T, kBigBM) : cdiv(p.T * p.k, kBigBM) + p.E;
       if (up && dual)
@@ -1844,10 +1951,14 @@ static hipError_t ffn_pass(const LayerParams& p, bool bf16, bool up, bool shared
       else
         launch_ffn_big<2>(a, big_mt, p.n_cu, st);
     } else if (up && dual)
-      launch_ffn_mma<UpDualTile, true>(a, max_mt, p.n_cu, st);
+      launch_ffn_up<UpDualTile, UpDualHalf>(a, max_mt, row_tiles, p.n_cu, st);
     else if (up)
-      launch_ffn_mma<UpTile, true>(a, max_mt, p.n_cu, st);
-    else
+      launch_ffn_up<UpTile, UpHalf>(a, max_mt, row_tiles, p.n_cu, st);
+    else if (shared) {
+      const dim3 grid(min(max_mt * cdiv(a.N, DownTile64::BN), p.n_cu));
+      hipLaunchKernelGGL((k_ffn_dense_down<DownTile, DownTile128, DownTile64>), grid,
+                         dim3(DownTile::THREADS), 0, st, a);
+    } else
       launch_ffn_mma<DownTile, false>(a, max_mt, p.n_cu, st);
   } else if (f32_slices(K)) {
     FfnArgs a{static_cast<const bf16_t*>(X), x_idx, static_cast<const bf16_t*>(w0),

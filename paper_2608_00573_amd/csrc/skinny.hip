@@ -393,7 +393,8 @@ __global__ __launch_bounds__(skinny::THREADS) void k_ffn_skinny(FfnArgs a) {
   __shared__ __align__(16) char lds[skinny::LDS];
   const int dense_m1 = a.dense_rows ? *a.dense_rows : 0;
   // (wave-uniform, as the addresses of the weights have to be)
-  const int n_mt = __builtin_amdgcn_readfirstlane(a.dense_rows ? (dense_m1 > 0 ? 1 : 0) : *a.n_tiles);
+  const int n_mt = __builtin_amdgcn_readfirstlane(
+      a.dense_rows ? (dense_m1 + kSkinnyTokens - 1) / kSkinnyTokens : *a.n_tiles);
   const int npt = a.N / skinny::COLS;  // groups per row tile; N is a multiple of 64
   long u, u1;
   skinny_range((long)n_mt * npt, u, u1);
@@ -404,14 +405,15 @@ __global__ __launch_bounds__(skinny::THREADS) void k_ffn_skinny(FfnArgs a) {
     // the block's groups of one row tile
     const int mt = (int)(u / npt), c0 = (int)(u - (long)mt * npt);
     const int groups = min((int)(u1 - u), npt - c0);
-    int e = 0, m0 = 0, m1 = dense_m1;
+    int e = 0, m0 = mt * kSkinnyTokens, m1 = dense_m1;
     if (!a.dense_rows) {
       const int4 tl = a.tiles[mt];
       e = __builtin_amdgcn_readfirstlane(tl.x);
       m0 = __builtin_amdgcn_readfirstlane(tl.y);
       m1 = __builtin_amdgcn_readfirstlane(tl.z);
     }
-    // a tile of a batch of at most kSkinnyTokens tokens has no more rows
+    // an expert's tile of a batch of at most kSkinnyTokens tokens has no more
+    // rows; dense tiles are that long
     const int rows = min(m1 - m0, kSkinnyTokens);
     const int n0 = c0 * skinny::COLS, n1 = n0 + groups * skinny::COLS;
     if (rows <= 16)

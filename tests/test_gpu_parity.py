@@ -170,6 +170,27 @@ def test_live_down_splits(T, k, E, d, F):
     _run_and_compare(cfg)
 
 
+@pytest.mark.parametrize("act,T,k,E,d,F,Fs", [
+    ("swiglu", 300, 2, 8, 64, 4224, 0),    # 33 column tiles: more than a round, short K
+    ("swiglu", 500, 2, 2, 2048, 4224, 0),  # a full round, the rest in halves
+    ("relu", 1000, 1, 2, 2112, 8448, 0),
+    ("relu", 90, 1, 4, 128, 512, 0),       # less than a round: halves only
+    ("swiglu", 90, 1, 2, 128, 192, 0),     # a column tile cut short: no halves
+    ("swiglu", 101, 1, 2, 192, 64, 320),   # shared expert: a second pass over the weights
+    ("relu", 128, 1, 2, 64, 64, 1152),     # ... of two whole row tiles
+    ("swiglu", 129, 1, 2, 320, 64, 576),   # its down GEMM in 64-column tiles,
+    ("swiglu", 1900, 1, 2, 1152, 64, 64),  # ... 128 (15 row tiles x 18 of 64 columns)
+    ("swiglu", 2047, 1, 2, 2112, 64, 128),  # ... and 256 (16 x 17 of 128)
+])
+def test_last_round_halves_and_shared_expert_tiles(act, T, k, E, d, F, Fs):
+    # no budget: every token runs its own experts, so the tile counts are these
+    cfg = workload("tiny_fp32", dtype="bf16", act=act, n_tokens=T, top_k=k, n_experts=E,
+                   n_local=max(1, E // 2), d_model=d, d_ff=F, d_ff_shared=Fs, vocab_exit=70,
+                   normalize_topk=1, n_layers=2)
+    inp = make_inputs(cfg)
+    _run_and_compare(cfg, pol=dict(inp["policy"], budget=0.0))
+
+
 def test_wide_model_exit_head_ragged():
     # d_model 2048 at 1100 tokens: the exit head takes 256 x 256 tiles with
     # 4 wavefronts; 1100 tokens and 1000 vocabulary rows leave partial token
