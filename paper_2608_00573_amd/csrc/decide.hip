@@ -1338,9 +1338,11 @@ __global__ __launch_bounds__(1024) void k_scan(LayerParams p) {
 __device__ __forceinline__ void fused_scan(const LayerParams& p, int nb, int* s_cnt, int* s_x,
                                            int* s_seg, int* s_wave, int* s_off, int* s_xoff) {
   const int E = p.E, tid = threadIdx.x, b_me = blockIdx.x;
-  const int n_c = nb * E;
+  // (every block of the grid: those past nb are not read below, and the loads
+  // need not wait for the live count)
+  const int n_c = gridDim.x * E;
   for (int i = tid; i < n_c; i += blockDim.x) s_cnt[i] = p.blk_cnt[i];
-  for (int b = tid; b < nb; b += blockDim.x) s_x[b] = p.blk_xcnt[b];
+  for (int b = tid; b < (int)gridDim.x; b += blockDim.x) s_x[b] = p.blk_xcnt[b];
   __syncthreads();
   // thread (segment g, expert e) sums its run of blocks; the segment holding
   // this block also sums the blocks before it
@@ -1367,6 +1369,64 @@ __device__ __forceinline__ void fused_scan(const LayerParams& p, int nb, int* s_
       tot += v;
     }
     pre += b_me < nb ? s_off[tid] : 0;
+  }
+  if (E <= 64) {
+    // one wavefront scans the experts and another adds the executed counts:
+    // the block-wide scans larger models need are nine barriers more.  With the
+    // early loads of k_bucket, layer step or stack: two tiny layers 89.5 -> 85.3
+    // us, six Switch-shaped ones of 64 tokens 410 -> 397, Mixtral shapes, 1
+    // token: 187 -> 185
+    if (tid < 64) {
+      const int nt_e = (tot + p.bm - 1) / p.bm;
+      int off = tot, toff = nt_e;  // inclusive
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(off, o), z = __shfl_up(toff, o);
+        if (tid >= o) {
+          off += y;
+          toff += z;
+        }
+      }
+      const int total = __shfl(off, 63), ttotal = __shfl(toff, 63);
+      off -= tot;
+      toff -= nt_e;
+      if (tid < E) s_off[tid] = off + pre;
+      if (b_me == 0) {
+        const int distinct = __popcll(__ballot(tot > 0));
+        if (tid < E) {
+          p.exp_off[tid] = off;
+          p.exp_toff[tid] = toff;
+          for (int u = 0; u < nt_e; ++u)
+            p.tiles[toff + u] = make_int4(tid, off + u * p.bm, off + tot, 0);
+        }
+        if (tid == 0) {
+          p.exp_off[E] = total;
+          p.counts[kCntRows] = total;
+          p.counts[kCntTiles] = ttotal;
+          if (p.tr_counters) {
+            p.tr_counters[6] = total;
+            p.tr_counters[7] = distinct;
+          }
+        }
+      }
+    } else if (tid < 128) {
+      int all = 0, mine = 0;
+      for (int b = tid - 64; b < nb; b += 64) {
+        const int v = s_x[b];
+        all += v;
+        mine += b < b_me ? v : 0;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        all += __shfl_xor(all, o);
+        mine += __shfl_xor(mine, o);
+      }
+      if (tid == 64) {
+        *s_xoff = mine;
+        if (b_me == 0) p.counts[kCntExec] = all;
+      }
+    }
+    return;  // (the caller's barrier follows)
   }
   __syncthreads();
   int total = 0, ttotal = 0;
@@ -1415,6 +1475,15 @@ __global__ __launch_bounds__(256) void k_bucket(LayerParams p) {
   const int base = blockIdx.x * p.rb;
   const int k = p.k, E = p.E;
   const int tid = threadIdx.x;
+  // thread (token i, slot j).  What it reads of its token is loaded before the
+  // live count is known (positions below T lie inside the buffers)
+  const int i = tid / k, j = tid - i * k;
+  const int pos = base + i;
+  const bool slot = i < p.rb && pos < p.T, token = tid < p.rb && base + tid < p.T;
+  const int slot_e = slot ? p.tok_exec[(size_t)pos * k + j] : -1;
+  const int slot_t = slot ? p.active_idx[pos] : 0;
+  const int action = token ? p.tok_action[base + tid] : TRIMMOE_ACT_SKIP;
+  const int token_t = token ? p.active_idx[base + tid] : 0;
   if constexpr (FUSED) {
     __shared__ int s_cnt[kFusedScanEntries];
     __shared__ int s_x[kFusedScanBlocks];
@@ -1436,26 +1505,21 @@ __global__ __launch_bounds__(256) void k_bucket(LayerParams p) {
   const int nt = min(p.rb, n_a - base);
   if (tid == 0) s_xmask = 0u;
   __syncthreads();
-  // thread (token i, slot j); a token's merged rows are distinct experts
-  // packed at the front of its slots, so the rows of e before token i's
-  // are one per earlier block token that holds e
-  const int i = tid / k, j = tid - (tid / k) * k;
-  const int pos = base + i;
-  int e = -1;
-  if (tid < nt * k) {
-    e = p.tok_exec[(size_t)pos * k + j];
-    if (e >= 0) atomicOr(&s_emask[e], 1u << i);
-  }
-  if (tid < nt && p.tok_action[base + tid] == TRIMMOE_ACT_EXEC) atomicOr(&s_xmask, 1u << tid);
+  // a token's merged rows are distinct experts packed at the front of its
+  // slots, so the rows of e before token i's are one per earlier block token
+  // that holds e
+  const int e = tid < nt * k ? slot_e : -1;
+  if (e >= 0) atomicOr(&s_emask[e], 1u << i);
+  if (tid < nt && action == TRIMMOE_ACT_EXEC) atomicOr(&s_xmask, 1u << tid);
   __syncthreads();
   if (e >= 0) {
     const int row = s_off[e] + __popc(s_emask[e] & ((1u << i) - 1u));
     p.tok_row[(size_t)pos * k + j] = row;
-    p.row_src[row] = p.active_idx[pos];
+    p.row_src[row] = slot_t;
   }
   if (tid < nt && ((s_xmask >> tid) & 1u)) {
     const int xidx = s_xoff + __popc(s_xmask & ((1u << tid) - 1u));
-    p.exec_list[xidx] = p.active_idx[base + tid];
+    p.exec_list[xidx] = token_t;
     p.exec_pos[xidx] = base + tid;
   }
 }

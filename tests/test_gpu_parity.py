@@ -121,6 +121,18 @@ def test_route_blocks(dtype, E, k, d, T):
     assert (gtr["kind"] == O.KIND_SUB).any()
 
 
+@pytest.mark.parametrize("E,T,p_exit", [
+    (64, 500, 0.5),    # the last expert count one wavefront scans (63 route blocks)
+    (65, 500, 0.5),    # ... and the first of the block-wide scans
+    (1, 1023, 0.5),    # one expert over every route block
+    (33, 100, 0.0),    # later layers route no token
+])
+def test_bucket_scans(E, T, p_exit):
+    cfg = workload("tiny_fp32", n_tokens=T, n_experts=E, n_local=max(1, E // 2), d_ff=32,
+                   vocab_exit=50, n_layers=3, p_exit=p_exit)
+    _run_and_compare(cfg)
+
+
 @pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
     ("swiglu", 1, 1, 1, 64, 64, 0, 1000),       # K of two k-steps: half the wavefronts idle
     ("relu", 16, 1, 2, 128, 192, 64, 17),       # one full 16-row tile; one row past a group
