@@ -1341,12 +1341,21 @@ struct ExitSrc {
         const LanePair pm = lanes_xor32(m);
         m = fmaxf(pm.a, pm.b);
       }
+      // (in pairs: a chain of sixteen would round each small term at the size of
+      // the largest, and its error showed in xi beside the 16-row tiles')
       float sum = 0.f;
       if (m != ninf) {
 #pragma unroll
-        for (int i = 0; i < T::TM; ++i)
+        for (int i = 0; i < T::TM; ++i) {
+          float e[16];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sum += expf(acc[i][jj][r] - m);
+          for (int r = 0; r < 16; ++r) e[r] = expf(acc[i][jj][r] - m);
+#pragma unroll
+          for (int n = 8; n > 0; n >>= 1)
+#pragma unroll
+            for (int r = 0; r < n; ++r) e[r] += e[r + n];
+          sum += e[0];
+        }
       }
       {
         const LanePair ps = lanes_xor32(sum);
