@@ -78,8 +78,22 @@ struct LdsRead<1, STRIDE> {
     asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v[0]) : "v"(a) : "memory");
   }
 };
-__device__ __forceinline__ void lds_put(uint32_t a, f32x4_t v) {
-  asm volatile("ds_write_b128 %0, %1" ::"v"(a), "v"(v) : "memory");
+// K parts of a sum; the remarks name the layout of the sum area (bytes of a
+// wavefront's parts, whether the halves of the area alternate), by which the
+// check of the generated code tells the streams apart
+template <int PART, bool PAR>
+__device__ __forceinline__ void part_put(uint32_t a, f32x4_t v) {
+  asm volatile("ds_write_b128 %0, %1 ; part write %2 %3" ::"v"(a), "v"(v), "n"(PART), "n"(PAR)
+               : "memory");
+}
+template <int PART, bool PAR>
+__device__ __forceinline__ void parts_get(uint32_t a, f32x4_t (&v)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %4 ; part read %5 %8\n\tds_read_b128 %1, %4 offset:%5\n\t"
+      "ds_read_b128 %2, %4 offset:%6\n\tds_read_b128 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(a), "n"(PART), "n"(2 * PART), "n"(3 * PART), "n"(PAR)
+      : "memory");
 }
 
 // range of units of this block, blocks of one XCD (dealt b % 8) in a row
@@ -105,7 +119,8 @@ struct Stream {
   static constexpr int OPS = NW * U + MT * U;   // vector-memory operations of a set
   // K parts of GR groups meet at once, a wavefront adding the tile (group,
   // token tile) of its number; PAR: the buffer alternates, so that a round
-  // needs one barrier
+  // needs one barrier (while the layout stays: between streams of different
+  // shapes the block needs one more)
   static constexpr int GR = skinny::WAVES * NB * G * MT * 1024 <= skinny::RED && G * MT <= skinny::WAVES ? G : 1;
   static constexpr int PART = NB * GR * MT * 1024;
   static constexpr bool PAR = 2 * skinny::WAVES * PART <= skinny::RED;
@@ -304,14 +319,14 @@ __device__ __forceinline__ bool skinny_sum(char* lds, int& par,
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
         f32x4_t t = acc[o][g0 + g][m];
-        lds_put(red + wave * T::PART + ((o * GR + g) * MT + m) * 1024, t);
+        part_put<T::PART, T::PAR>(red + wave * T::PART + ((o * GR + g) * MT + m) * 1024, t);
       }
   lds_barrier();
   if (wave < T::TILES) {
 #pragma unroll
     for (int o = 0; o < NB; ++o) {
       f32x4_t p[4];
-      LdsRead<4, T::PART>::get(red + (o * T::TILES + wave) * 1024, p);
+      parts_get<T::PART, T::PAR>(red + (o * T::TILES + wave) * 1024, p);
       v[o] = p[0];
 #pragma unroll
       for (int w = 1; w < 4; ++w)
@@ -381,6 +396,9 @@ __device__ __forceinline__ void skinny_ffn_rows(const FfnArgs& a, char* lds, int
   };
   const int units = (n1 - n0 + skinny::COLS * G - 1) / (skinny::COLS * G);
   skinny_stream<T>(lds, xs, units, a.K / skinny::KSTEP, wbase, wrows, epi);
+  // the block's next tile may be of another width, which lays the sums out
+  // anew: every wavefront has to be past its reads of the last one first
+  if constexpr (T::PAR) lds_barrier();
 }
 
 // the widest batches halve their activation traffic with four groups per unit

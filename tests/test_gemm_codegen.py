@@ -62,12 +62,12 @@ def skinny_asm(tmp_path_factory):
     return _compile(tmp_path_factory, "skinny.hip")
 
 
-def _function(text, name):
+def _function(text, name, remarks=False):
     start = text.index(f"\n{name}:") + 1
     end = text.index(".Lfunc_end", start)
     body = []
     for line in text[start:end].splitlines()[1:]:
-        line = line.split(";")[0].strip()
+        line = (line if remarks and "; part " in line else line.split(";")[0]).strip()
         if line and not line.startswith("."):
             body.append(line)
         elif re.match(r"^\.LBB\d+_\d+:", line):
@@ -291,6 +291,59 @@ def test_weight_streaming_kernels(skinny_asm):
         for i, b in enumerate(body):
             if b.startswith("buffer_load") and b.endswith("lds"):
                 assert not any(x.startswith("s_cbranch_execnz") for x in body[i:i + 4]), (name, b)
+
+
+_PART_READ = re.compile(r"; part read (\w+) (\d)")
+_PART_WRITE = re.compile(r"; part write (\w+) (\d)")
+
+
+def _part_races(body):
+    """Writes of K parts that a wavefront may issue while another one of its
+    block still reads the parts of an earlier sum: writes reachable from a read
+    with no barrier in between, unless both use one layout whose halves
+    alternate (the write then goes to the other half)."""
+    succ = _cfg(body)
+    found = []
+    for i, ins in enumerate(body):
+        m = _PART_READ.search(ins)
+        if not m:
+            continue
+        stack, seen = list(succ(i)), set()
+        while stack:
+            j = stack.pop()
+            if j in seen:
+                continue
+            seen.add(j)
+            cur = body[j]
+            if cur.startswith("s_barrier"):
+                continue
+            w = _PART_WRITE.search(cur)
+            if w and (w.groups() != m.groups() or w.group(2) == "0"):
+                found.append((ins, cur))
+            stack.extend(succ(j))
+    return found
+
+
+def test_weight_streaming_sums_are_read_before_their_area_is_written(skinny_asm):
+    names = re.findall(r"^(_ZN7trimmoe\w*k_(?:ffn|exit)_skinny\w*):", skinny_asm, re.M)
+    for name in names:
+        body = _function(skinny_asm, name, remarks=True)
+        assert any(_PART_READ.search(b) for b in body) and any(_PART_WRITE.search(b) for b in body)
+        bad = _part_races(body)
+        assert not bad, (name, len(bad), bad[:4])
+
+
+def test_part_race_checker_finds_planted_races():
+    def body(w, barrier=()):
+        return ["ds_read_b128 v[0:3], v9 ; part read 2048 1", *barrier, f"ds_write_b128 v8, v[0:3] ; {w}",
+                "s_endpgm"]
+    assert not _part_races(body("part write 2048 1"))
+    assert _part_races(body("part write 4096 1"))
+    assert not _part_races(body("part write 4096 1", ["s_barrier"]))
+    # one layout whose halves do not alternate
+    one = ["ds_read_b128 v[0:3], v9 ; part read 8192 0", "ds_write_b128 v8, v[0:3] ; part write 8192 0",
+           "s_endpgm"]
+    assert _part_races(one)
 
 
 def test_race_checker_finds_planted_races():

@@ -151,6 +151,47 @@ def test_weight_streaming_edges(act, T, k, E, d, F, Fs, V):
     _run_and_compare(cfg)
 
 
+def _width_changes(rows, N):
+    """Changes of the row-tile width (up to 16, 32 or more rows) inside one
+    block's range of 16-column groups (row tiles of experts with rows, N
+    columns each, dealt evenly to a block per CU)."""
+    w = [1 if r <= 16 else 2 if r <= 32 else 4 for r in rows if r > 0]
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    npt, out = N // 16, set()
+    total = npt * len(w)
+    for v in range(n_cu):
+        ts = sorted({g // npt for g in range(total * v // n_cu, total * (v + 1) // n_cu)})
+        out |= {(w[a], w[b]) for a, b in zip(ts, ts[1:]) if w[a] != w[b]}
+    return out
+
+
+@pytest.mark.parametrize("skew", [(1.6, -1.0, 0.5, -1.0, 1.6, 0.5, -1.0),
+                                  (-1.0, 0.5, 1.6, -1.0, 1.6, -1.0, 0.5)])
+@pytest.mark.parametrize("act,d,F", [
+    ("swiglu", 64, 2496),   # K of two k-steps: wavefronts without one join the sums at once
+    ("relu", 128, 2496),
+    ("relu", 192, 2496),
+    ("swiglu", 2496, 64),   # ... in the down projection
+    ("relu", 2496, 128),
+    ("swiglu", 2496, 192),
+    ("swiglu", 1088, 2496),  # long K, both projections
+])
+def test_weight_streaming_row_tiles_of_different_width(act, d, F, skew):
+    # a block goes on from one expert's row tile to another's of a different
+    # width: the sums' LDS area changes its layout
+    cfg = workload("tiny_fp32", dtype="bf16", act=act, n_tokens=64, top_k=2, n_experts=len(skew),
+                   n_local=3, d_model=d, d_ff=F, vocab_exit=130, normalize_topk=1, n_layers=2)
+
+    def edit(inp):
+        for L in inp["layers"]:
+            L["b_router"] = torch.tensor(skew) * (0.02 * d ** 0.5)
+    # no budget: every token runs its own experts
+    pol = dict(make_inputs(cfg, with_layers=False)["policy"], budget=0.0)
+    _, _, gtr, _, _, _ = _run_and_compare(cfg, pol=pol, edit=edit)
+    rows = [int((gtr["exec"][0] == e).sum()) for e in range(len(skew))]
+    assert _width_changes(rows, F) | _width_changes(rows, d), rows
+
+
 @pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
     ("relu", 64, 1, 8, 64, 256, 0, 130),        # two K slices; a partial vocabulary tile
     ("swiglu", 65, 2, 4, 96, 160, 64, 1),       # three slices; the 128-token exit tile
