@@ -435,7 +435,8 @@ int trimmoe_place_replicas(int32_t n_servers, int32_t n_layers, int32_t n_expert
  * anything is enqueued.
  *
  * trimmoe_head_argmax: argmax[q] = argmax_v (w_head[v] . h[q] + b_head[v])
- * over the V rows of an output head w_head [V, d] (ties to the lower v): the
+ * over the V rows of an output head w_head [V, d] (ties to the lower v; a NaN
+ * logit is never the largest, and 0 where none is above -inf): the
  * prediction of a representation, from which the consistency labels of
  * Eq. (22) follow.  h [n_rows, d] and w_head in `dtype` (bf16: d a multiple
  * of 64, both 16-byte aligned); b_head fp32 [V] or NULL; argmax int32

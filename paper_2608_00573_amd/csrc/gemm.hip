@@ -1381,7 +1381,8 @@ struct ExitSrc {
     }
   }
   // per (token, vocabulary tile): the largest logit and its vocabulary row
-  // (ties to the lower row), the row stored as the float's bit pattern
+  // (ties to the lower row; the tile's first row where none is above -inf, as
+  // of NaN logits), the row stored as the float's bit pattern
   __device__ __forceinline__ void epilogue_argmax(const Desc& d, Acc<T>& acc) const {
     const int v0 = d.mt * T::BM, j0 = d.nt * T::BN;
     const int a_valid = min(T::BM, a.V - v0);
@@ -1391,7 +1392,7 @@ struct ExitSrc {
 #pragma unroll
     for (int jj = 0; jj < T::TN; ++jj) {
       float m = -__builtin_inff();
-      int mi = 0x7fffffff;
+      int mi = 0;
 #pragma unroll
       for (int i = 0; i < T::TM; ++i)
 #pragma unroll
@@ -1629,7 +1630,8 @@ __device__ __forceinline__ void exit_big_epilogue(const ExitArgs& a, const TileS
 }
 
 // argmax partials of tile j: per token column the largest logit and its
-// vocabulary row (ties to the lower row), combined as above
+// vocabulary row (ties to the lower row; the tile's first row where none is
+// above -inf), combined as above
 __device__ __forceinline__ void exit_big_argmax(const ExitArgs& a, const TileSched& S, int n_x,
                                                 int jt, const AccBig& acc,
                                                 float2 (*s_part)[big::BN], int wm, int wn,
@@ -1654,10 +1656,11 @@ __device__ __forceinline__ void exit_big_argmax(const ExitArgs& a, const TileSch
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     m = -__builtin_inff();
-    mi = 0x7fffffff;
+    mi = 0;
     if (full) {
       // the largest logit, then the lowest row that holds it (last of a pass
       // from the highest row down)
+      mi = 128;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1666,7 +1669,7 @@ __device__ __forceinline__ void exit_big_argmax(const ExitArgs& a, const TileSch
       for (int i = 7; i >= 0; --i)
 #pragma unroll
         for (int r = 3; r >= 0; --r) mi = acc[i][j][r] == m ? 16 * i + r : mi;
-      mi = mi < 128 ? r0 + mi : mi;
+      mi = mi < 128 ? r0 + mi : 0;
     } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i)

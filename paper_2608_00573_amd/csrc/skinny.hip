@@ -475,7 +475,7 @@ __device__ __forceinline__ void skinny_exit_rows(const ExitArgs& a, char* lds, i
   const float ninf = -__builtin_inff();
   const float kLog2e = 1.4426950408889634f;
   float M = ninf, S = 0.f;  // of the lane's token (wavefront m < MT: tile m), its rows 4 q .. + 4
-  int R = 0x7fffffff;
+  int R = v0;  // ... while no logit is above -inf
   auto group = [&](int r0, const f32x4_t& v) {
     float y[4];
 #pragma unroll

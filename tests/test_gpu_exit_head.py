@@ -45,6 +45,44 @@ def test_head_argmax_matches_oracle(dtype, V, d, Q):
     assert np.array_equal(got[clear], want[clear])
 
 
+@pytest.mark.parametrize("dtype,V,d,Q", [
+    (torch.float32, 300, 96, 7),          # 128 x 32 fp32 tiles
+    (torch.float32, 1000, 64, 100),       # 128 x 128 fp32 tiles
+    (torch.float32, 50, 40, 33),          # FMA kernel
+    (torch.bfloat16, 1003, 64, 7),        # weight-streaming, short K
+    (torch.bfloat16, 5000, 576, 40),      # ... long K
+    (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles
+    (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
+    (torch.bfloat16, 700, 2048, 1030),    # large-group tiles
+])
+def test_head_argmax_without_a_largest_logit(dtype, V, d, Q):
+    # NaN never wins, and where no logit is above -inf the answer is row 0
+    log(f"[exit-head] argmax NaN, -inf {dtype} V={V} d={d} Q={Q}")
+    W, Wn = _mat(11, 1, (V, d), 0.02, dtype)
+    H, Hn = _mat(12, 2, (Q, d), 1.0, dtype)
+    nan_rows = np.arange(1, Q, 3)
+    Hd = H.to(DEV)
+    Hd[torch.from_numpy(nan_rows).to(DEV)] = float("nan")
+    got = abi.trimmoe_head_argmax(W.to(DEV), Hd).cpu().numpy()
+    assert (got[nan_rows] == 0).all()
+    rest = np.setdiff1d(np.arange(Q), nan_rows)
+    want, margin = X.head_argmax(Wn, Hn)
+    clear = rest[margin[rest] > 1e-5]
+    assert np.array_equal(got[clear], want[clear])
+    # a bias of -inf everywhere
+    none = torch.full((V,), -float("inf"), device=DEV)
+    got = abi.trimmoe_head_argmax(W.to(DEV), Hd, none).cpu().numpy()
+    assert (got == 0).all()
+    # every fifth vocabulary row is NaN, the first one too
+    Wd = W.to(DEV)
+    Wd[::5] = float("nan")
+    got = abi.trimmoe_head_argmax(Wd, H.to(DEV)).cpu().numpy()
+    keep = np.setdiff1d(np.arange(V), np.arange(0, V, 5))
+    want, margin = X.head_argmax(Wn[keep], Hn)
+    clear = margin > 1e-5
+    assert np.array_equal(got[clear], keep[want[clear]])
+
+
 def test_head_argmax_of_unaligned_fp32_operands():
     # fp32 operands need no alignment: an odd offset takes the FMA kernel
     W, Wn = _mat(13, 1, (10, 64), 0.02, torch.float32)
