@@ -322,8 +322,10 @@ int run_layer(const trimmoe_model* m, int l, const trimmoe_policy* pol, const tr
       ncu <= 0)
     return TRIMMOE_ERR_HIP;
   P.n_cu = ncu;
-  P.n_vtiles = exit_vtiles(m->dtype == TRIMMOE_BF16, f32_slices(m->d_model), s->n_tokens,
-                           m->vocab_exit, ncu);
+  P.exit_stream = exit_streams(m->dtype == TRIMMOE_BF16, false, s->n_tokens, m->vocab_exit,
+                               m->d_model);
+  P.n_vtiles = exit_vtiles(m->dtype == TRIMMOE_BF16, f32_slices(m->d_model), P.exit_stream,
+                           s->n_tokens, m->vocab_exit, ncu);
   P.clk = clock_record_for(dev);
   const bool bf16 = m->dtype == TRIMMOE_BF16;
   const bool last = l == m->n_layers - 1;
@@ -598,7 +600,8 @@ int trimmoe_head_argmax(int32_t dtype, int32_t vocab, int32_t d_model, int32_t n
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return TRIMMOE_ERR_HIP;
-  nvt = exit_vtiles(bf16, f32_mma(w_head, h, d_model), n_rows, vocab, ncu);
+  nvt = exit_vtiles(bf16, f32_mma(w_head, h, d_model),
+                    exit_streams(bf16, true, n_rows, vocab, d_model), n_rows, vocab, ncu);
   hipStream_t st = static_cast<hipStream_t>(stream);
   int32_t* n_dev = static_cast<int32_t*>(workspace);
   float2* partials = reinterpret_cast<float2*>(static_cast<char*>(workspace) + 256);

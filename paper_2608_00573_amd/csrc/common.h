@@ -147,13 +147,38 @@ __host__ __device__ inline int frag_order(int kstep, int group, int row, int n) 
 inline int exit_tile_rows(bool bf16, int T) {
   return bf16 ? (T <= kSkinnyTokens ? kExitTileBF16Small : kExitTileBF16) : kExitTileF32;
 }
+// bf16 exit heads of up to kSkinnyTokens tokens that stream W (skinny.hip); the
+// others run 128 x 32 tiles (gemm.hip).  A wavefront of the streaming kernel
+// takes a quarter of K and every 16 rows of W end in a sum through LDS, so it
+// pays where rows are long; a block of it takes 128 rows of W or more, so
+// beyond 16 tokens it needs enough of them for three quarters of the CUs (below,
+// the tile's chain of K slices is shorter).  Kernel times on an MI355X, tiles and
+// streaming, W not in the cache (us): d = 768, V = 32000: 12.0 and 13.5 at 16
+// tokens, 16.8 and 20.0 at 64; d = 2048, V = 16000: 20.8 and 19.7 at 16, 22.8 and
+// 29.2 at 64; V = 32000: 32.6 and 24.9, 42.6 and 33.8; d = 4096, V = 4000: 32.8
+// and 29.8, 32.6 and 44.7; V = 32000: 59.6 and 42.5, 75.2 and 53.7.  Heads past the
+// last-level cache stream with shorter rows too (d = 1024, V = 150000: 55.0 and
+// 50.1, 90.2 and 84.9), but not at 17 to 32 tokens, one column of tiles (55.8 and
+// 68.8); there an argmax, which gathers a caller's rows, never does (d = 2048,
+// V = 32000: 33.8 and 35.5).  A head of one group of 16 rows is one short unit
+// (sigmoid, d = 768, 16 tokens: 9.3 and 6.1).
+constexpr int kStreamExitDModel = 2048;
+constexpr int kStreamExitVocab = 24576;
+inline bool exit_streams(bool bf16, bool argmax, int T, int V, int d) {
+  if (!bf16 || T > kSkinnyTokens) return false;
+  const bool wide = d >= kStreamExitDModel, huge = (long long)V * d >= 1ll << 27;
+  if (T <= 16) return V <= 16 || wide || huge;
+  if (V <= 16) return T <= 32 || wide;
+  if (T <= 32) return !argmax && wide && V >= kStreamExitVocab;
+  return (wide && V >= kStreamExitVocab) || huge;
+}
 // exit partials per token of a launch on n_cu compute units (never more than
 // the exit_tile_rows tiles the workspace is sized for); mma_f32: an fp32 head
-// in fp32 MFMAs
-inline int exit_vtiles(bool bf16, bool mma_f32, int T, int V, int n_cu) {
+// in fp32 MFMAs; streams: one partial per block (exit_streams)
+inline int exit_vtiles(bool bf16, bool mma_f32, bool streams, int T, int V, int n_cu) {
   const int rows = !bf16 && mma_f32 ? kExitTileF32Mma : exit_tile_rows(bf16, T);
   const int n = (V + rows - 1) / rows;
-  return bf16 && T <= kSkinnyTokens && n > n_cu ? n_cu : n;
+  return streams && n > n_cu ? n_cu : n;
 }
 // fp32 GEMM tile
 constexpr int kF32Tile = 16;
@@ -282,6 +307,7 @@ struct LayerParams {
                        // in operand order for the weight-streaming exit head)
   float2* partials;    // [T, n_vtiles] (max, sum exp) per vocabulary tile
   int n_vtiles;
+  bool exit_stream;    // the exit head streams W (exit_streams)
   int max_tiles;
   int n_cu;            // compute units of the device (persistent grids)
   // engine-clock record (measurement): [class][2] sums of core cycles and

@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(256) void k_combine(LayerParams p) {
     ST* xr = static_cast<ST*>(p.hx) + (size_t)j * p.d + c;
     if constexpr (sizeof(ST) == 2) {
       // the weight-streaming exit head reads hx in operand order
-      if (p.T <= kSkinnyTokens) {
+      if (p.exit_stream) {
         const int b = j & ~15;
         xr = static_cast<ST*>(p.hx) + (size_t)b * p.d +
              frag_order(c >> 5, (c >> 3) & 3, j - b, min(16, n_x - b));

@@ -1277,6 +1277,9 @@ using ExitTile = Tile<kExitTileBF16, 128, 1, 4, 2>;
 // ring (the 128-token tile keeps three stages, and its finer token tiles
 // balance the persistent grid better at small n_x)
 using ExitWide = Tile<kExitTileBF16, 256, 1, 4, 2>;
+// decode-sized batches whose head does not stream W (exit_streams): 32 token
+// columns, 128 vocabulary rows, so that the MFMA work is not 4x padding
+using ExitSmall = Tile<kExitTileBF16Small, 32, 1, 4, 1>;
 
 template <class T, bool ARGMAX = false>
 struct ExitSrc {
@@ -2029,11 +2032,14 @@ hipError_t launch_exit_head(const LayerParams& p, bool bf16, hipStream_t st) {
     ExitArgs a{static_cast<const bf16_t*>(p.w_exit), static_cast<const bf16_t*>(p.hx), p.b_exit,
                &p.counts[kCntExec], p.V, p.d, p.n_vtiles, p.partials,
                p.clk ? p.clk + 2 * TRIMMOE_CLASS_EXIT : nullptr};
-    if (p.T <= kSkinnyTokens) return launch_exit_skinny(a, false, st);
+    if (p.exit_stream) return launch_exit_skinny(a, false, st);
     // persistent: at most one block per CU, none beyond the tile bound
     if (big_exit(true, p.T, p.V, p.d)) {
       const dim3 grid(min(p.n_vtiles * cdiv(p.T, big::BN), p.n_cu));
       hipLaunchKernelGGL(k_exit_big, grid, dim3(big::THREADS), 0, st, a);
+    } else if (p.T <= kSkinnyTokens) {
+      const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitSmall::BN), p.n_cu));
+      hipLaunchKernelGGL(k_exit_mma<ExitSmall>, grid, dim3(ExitSmall::THREADS), 0, st, a);
     } else if (p.T >= kWideTokens) {
       const dim3 grid(min(p.n_vtiles * cdiv(p.T, ExitWide::BN), p.n_cu));
       hipLaunchKernelGGL(k_exit_mma<ExitWide>, grid, dim3(ExitWide::THREADS), 0, st, a);
@@ -2067,12 +2073,15 @@ hipError_t launch_head_argmax_partials(bool bf16, const void* W, const float* bi
   if (bf16) {
     ExitArgs a{static_cast<const bf16_t*>(W), static_cast<const bf16_t*>(H), bias, n_rows_dev, V,
                K, n_vtiles, partials};
-    if (n_rows <= kSkinnyTokens) return launch_exit_skinny(a, true, st);
+    if (exit_streams(true, true, n_rows, V, K)) return launch_exit_skinny(a, true, st);
     // wide models and large batches on the large-group core, as the exit head
     // (V = 151936, d = 2048, 2048 rows: 1365 -> 1005 us)
     if (big_exit(true, n_rows, V, K)) {
       const dim3 grid(min(n_vtiles * cdiv(n_rows, big::BN), n_cu));
       hipLaunchKernelGGL(k_argmax_big, grid, dim3(big::THREADS), 0, st, a);
+    } else if (n_rows <= kSkinnyTokens) {
+      const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitSmall::BN), n_cu));
+      hipLaunchKernelGGL((k_exit_mma<ExitSmall, true>), grid, dim3(ExitSmall::THREADS), 0, st, a);
     } else if (n_rows >= kWideTokens) {
       const dim3 grid(min(n_vtiles * cdiv(n_rows, ExitWide::BN), n_cu));
       hipLaunchKernelGGL((k_exit_mma<ExitWide, true>), grid, dim3(ExitWide::THREADS), 0, st, a);

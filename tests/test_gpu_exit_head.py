@@ -27,9 +27,14 @@ def _mat(seed, tid, shape, sigma, dtype):
     (torch.float32, 1000, 64, 100),       # 128 x 128 fp32 tiles
     (torch.float32, 300, 96, 7),          # 128 x 32 fp32 tiles
     (torch.float32, 16, 40, 33),          # rows of partial K slices
-    (torch.bfloat16, 32128, 768, 50),     # decode-sized: weight-streaming, four row tiles
-    (torch.bfloat16, 1003, 64, 1),        # ... K of two k-steps, ragged vocabulary
-    (torch.bfloat16, 20, 2112, 17),       # ... two row tiles, one block
+    (torch.bfloat16, 32128, 768, 50),     # decode-sized: 128 x 32 tiles
+    (torch.bfloat16, 1003, 64, 1),        # ... one K slice, ragged vocabulary
+    (torch.bfloat16, 20, 2112, 17),       # ... a partial tile
+    # weight-streaming: one group of rows (at d = 64 one of the 16 rows of H has a margin of 9e-6,
+    # under the 1e-5 that counts as clear)
+    (torch.bfloat16, 16, 128, 16),
+    (torch.bfloat16, 1003, 2048, 16),     # ... long rows, ragged vocabulary
+    (torch.bfloat16, 24600, 2112, 40),    # ... from 33 rows on with many vocabulary rows
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles, ragged vocabulary
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
     (torch.bfloat16, 700, 2048, 1030),    # large-group tiles, ragged rows and vocabulary
@@ -49,8 +54,9 @@ def test_head_argmax_matches_oracle(dtype, V, d, Q):
     (torch.float32, 300, 96, 7),          # 128 x 32 fp32 tiles
     (torch.float32, 1000, 64, 100),       # 128 x 128 fp32 tiles
     (torch.float32, 50, 40, 33),          # FMA kernel
-    (torch.bfloat16, 1003, 64, 7),        # weight-streaming, short K
-    (torch.bfloat16, 5000, 576, 40),      # ... long K
+    (torch.bfloat16, 1003, 64, 7),        # 128 x 32 tiles
+    (torch.bfloat16, 16, 64, 7),          # weight-streaming, short K
+    (torch.bfloat16, 1003, 2112, 15),     # ... long K
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
     (torch.bfloat16, 700, 2048, 1030),    # large-group tiles

@@ -192,6 +192,33 @@ def test_weight_streaming_row_tiles_of_different_width(act, d, F, skew):
     assert _width_changes(rows, F) | _width_changes(rows, d), rows
 
 
+@pytest.mark.parametrize("T,d,V", [
+    (16, 64, 16),       # streaming: one group of rows, K of two k-steps
+    (32, 128, 16),
+    (33, 128, 16),      # ... and the first batch of its tiles
+    (16, 1984, 515),    # tiles: the longest rows that are not streamed
+    (1, 2048, 130),     # streaming: rows from here on,
+    (16, 2112, 515),    # ... up to 16 tokens
+    (17, 2112, 515),    # tiles
+    (64, 2048, 24575),
+    (64, 2048, 24576),  # streaming: and beyond 16 tokens with this many rows
+    (20, 2112, 24601),
+])
+def test_decode_sized_exit_heads(T, d, V):
+    # both exit kernels of a decode-sized batch at the borders of their rule
+    cfg = workload("tiny_fp32", dtype="bf16", n_tokens=T, n_experts=2, n_local=1, d_model=d, d_ff=64,
+                   vocab_exit=V, n_layers=2)
+    _run_and_compare(cfg)
+
+
+@pytest.mark.parametrize("T", [1, 16, 33, 64])
+@pytest.mark.parametrize("d", [64, 704, 2048])
+def test_decode_sized_sigmoid_heads(T, d):
+    cfg = workload("tiny_fp32", dtype="bf16", n_tokens=T, n_experts=2, n_local=1, d_model=d, d_ff=64,
+                   vocab_exit=1, n_layers=2, conf_mode="sigmoid")
+    _run_and_compare(cfg)
+
+
 @pytest.mark.parametrize("act,T,k,E,d,F,Fs,V", [
     ("relu", 64, 1, 8, 64, 256, 0, 130),        # two K slices; a partial vocabulary tile
     ("swiglu", 65, 2, 4, 96, 160, 64, 1),       # three slices; the 128-token exit tile
