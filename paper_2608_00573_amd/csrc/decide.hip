@@ -545,17 +545,27 @@ __host__ __device__ inline size_t la_carve(char* base, int E, int B, int k, int 
 // shapes 72 -> 23 at 16 tokens, 90 -> 39 at 4099; Mixtral 27 -> 15 at 32, 27 ->
 // 17 at 333, 31 -> 30 at 8192; fp32 at the Switch shape, 777 tokens, 74 -> 17
 // (serial FMA logits before); Switch at 4096 12 -> 12 (latency of its launch).
-template <int KS>
+// MANY: blocks of up to 16 experts in grids of more than a block per CU.  The
+// ring of 96 KB lets one block run on a CU at a time; with one of 36 KB three
+// do, and one block's top-k and decision run under another's loads.  Route
+// kernel, direct operand loads, 96 KB ring and this one (us): d = 64, 16384
+// tokens 11.3, 20.2 and 12.6, 65536 37.7, 70.1 and 30.4; d = 768, 32768 32.0, 42.8
+// and 28.5; d = 4096, 32768 86.5, 95.7 and 81.8.  With 17 experts or more the
+// large ring stays the better one (d = 256, 32 experts, 32768 tokens: 116 with
+// direct loads, 84 with it).
+constexpr int kManyKSteps = 4;
+template <int KS, bool MANY = false>
 struct LogitRing {
   static constexpr int SB = KS * 64;                     // bytes of a row segment
   static constexpr int CPR = SB / 16, RPI = 64 / CPR;    // chunks per row, rows per DMA
-  static constexpr int ROWS = KS == 16 ? 32 : KS == 8 ? 48 : KS == 4 ? 96 : 288;
+  static constexpr int ROWS = MANY || KS == 8 ? 48 : KS == 16 ? 32 : KS == 4 ? 96 : 288;
   static constexpr int NPW = (ROWS / RPI + kRouteWaves - 1) / kRouteWaves;  // DMAs per wavefront
-  static constexpr int STAGE = NPW * kRouteWaves * 1024;
-  static constexpr int NST = KS == 2 ? 2 : KS == 16 ? 3 : 4;
+  static constexpr int STAGE = ROWS / RPI * 1024;
+  static constexpr int NST = MANY ? 3 : KS == 2 ? 2 : KS == 16 ? 3 : 4;
   static constexpr int BYTES = NST * STAGE;
 };
 constexpr int kLogitRing = 96 * 1024;
+constexpr int kManyRing = LogitRing<kManyKSteps, true>::BYTES;
 static_assert(LogitRing<16>::BYTES <= kLogitRing && LogitRing<8>::BYTES <= kLogitRing && LogitRing<4>::BYTES <= kLogitRing &&
                   LogitRing<2>::BYTES <= kLogitRing,
               "one ring size");
@@ -567,10 +577,10 @@ static __host__ __device__ inline int logit_splits(int E) {
   return nct < kRouteWaves ? kRouteWaves / nct : 1;
 }
 
-template <bool F32, int KS>
+template <bool F32, int KS, bool MANY = false>
 __device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, char* ring, int base,
                                              int nt) {
-  using R = LogitRing<KS>;
+  using R = LogitRing<KS, MANY>;
   constexpr int ES = F32 ? 4 : 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int E = p.E, nct = (E + 15) >> 4, splits = logit_splits(E);
@@ -708,7 +718,7 @@ __device__ __forceinline__ void route_logits_any(const LayerParams& p, float* zs
 // candidate action of its tokens, one wavefront per token, its lanes over
 // (action, next-layer tuple) branches.  Phase 3: per-block expert histogram
 // for the bucketing.
-template <bool BF16, bool LA>
+template <bool BF16, bool LA, bool MANY = false>
 __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
   extern __shared__ __align__(16) float zs[];  // [logit_splits][RB][E] logits, K partial sums; LaLds
   __shared__ int s_cnt[TRIMMOE_MAX_EXPERTS];
@@ -759,6 +769,9 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
       char* ring = reinterpret_cast<char*>(zs + (size_t)logit_splits(E) * RB * E);
       static_assert(RB % 4 == 0, "the ring stays 16-byte aligned");
       route_logits_any<!BF16>(p, zs, ring, base, nt);
+    } else if constexpr (MANY) {
+      __shared__ __align__(16) char ring[kManyRing];
+      route_logits<!BF16, kManyKSteps, true>(p, zs, ring, base, nt);
     } else {
       __shared__ __align__(16) char ring[kLogitRing];
       route_logits_any<!BF16>(p, zs, ring, base, nt);
@@ -1740,6 +1753,9 @@ hipError_t launch_route(const LayerParams& p, bool bf16, hipStream_t st) {
         (const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, st, p);
+  } else if (bf16 && p.E <= 16 && nb > p.n_cu) {
+    // several blocks to a CU (LogitRing, MANY)
+    hipLaunchKernelGGL((k_route<true, false, true>), grid, block, parts, st, p);
   } else if (bf16) {
     hipLaunchKernelGGL((k_route<true, false>), grid, block, parts, st, p);
   } else {

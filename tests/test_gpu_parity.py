@@ -107,6 +107,8 @@ def test_decode_sized_relu_top1_ragged_up():
     ("bf16", 48, 5, 576, 40),     # three column tiles, two of the eight wavefronts idle
     ("bf16", 65, 4, 192, 700),    # five column tiles; 16-token blocks
     ("bf16", 129, 3, 128, 33),    # nine column tiles: a wavefront takes two
+    ("bf16", 16, 2, 64, 8225),    # more blocks than CUs, one K slice; a block of one token
+    ("bf16", 5, 2, 448, 8600),    # ... slices of the small ring with a remainder
     ("f32", 8, 2, 528, 5000),     # fp32 steps of 16 K; 32-token blocks
     ("f32", 33, 4, 72, 20),       # fp32 rows of a partial step: FMA logits
     ("f32", 256, 8, 64, 50),      # the most experts and slots
