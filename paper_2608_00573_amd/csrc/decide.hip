@@ -545,30 +545,37 @@ __host__ __device__ inline size_t la_carve(char* base, int E, int B, int k, int 
 // shapes 72 -> 23 at 16 tokens, 90 -> 39 at 4099; Mixtral 27 -> 15 at 32, 27 ->
 // 17 at 333, 31 -> 30 at 8192; fp32 at the Switch shape, 777 tokens, 74 -> 17
 // (serial FMA logits before); Switch at 4096 12 -> 12 (latency of its launch).
-// MANY: blocks of up to 16 experts in grids of more than a block per CU.  The
-// ring of 96 KB lets one block run on a CU at a time; with one of 36 KB three
-// do, and one block's top-k and decision run under another's loads.  Route
-// kernel, direct operand loads, 96 KB ring and this one (us): d = 64, 16384
-// tokens 11.3, 20.2 and 12.6, 65536 37.7, 70.1 and 30.4; d = 768, 32768 32.0, 42.8
-// and 28.5; d = 4096, 32768 86.5, 95.7 and 81.8.  With 17 experts or more the
-// large ring stays the better one (d = 256, 32 experts, 32768 tokens: 116 with
-// direct loads, 84 with it).
-constexpr int kManyKSteps = 4;
-template <int KS, bool MANY = false>
+// by column tiles of 16 experts, so that a slice has a k-step per K split
+template <int KS, int ROWS_, int NST_>
 struct LogitRing {
+  static constexpr int KSTEPS = KS, ROWS = ROWS_, NST = NST_;
   static constexpr int SB = KS * 64;                     // bytes of a row segment
   static constexpr int CPR = SB / 16, RPI = 64 / CPR;    // chunks per row, rows per DMA
-  static constexpr int ROWS = MANY || KS == 8 ? 48 : KS == 16 ? 32 : KS == 4 ? 96 : 288;
   static constexpr int NPW = (ROWS / RPI + kRouteWaves - 1) / kRouteWaves;  // DMAs per wavefront
   static constexpr int STAGE = ROWS / RPI * 1024;
-  static constexpr int NST = MANY ? 3 : KS == 2 ? 2 : KS == 16 ? 3 : 4;
   static constexpr int BYTES = NST * STAGE;
 };
+using Ring16 = LogitRing<16, 32, 3>;   // one tile, up to 16 tokens
+using Ring8 = LogitRing<8, 48, 4>;     // one
+using Ring4 = LogitRing<4, 96, 4>;     // up to four
+using Ring2 = LogitRing<2, 288, 2>;    // up to sixteen
 constexpr int kLogitRing = 96 * 1024;
-constexpr int kManyRing = LogitRing<kManyKSteps, true>::BYTES;
-static_assert(LogitRing<16>::BYTES <= kLogitRing && LogitRing<8>::BYTES <= kLogitRing && LogitRing<4>::BYTES <= kLogitRing &&
-                  LogitRing<2>::BYTES <= kLogitRing,
+static_assert(Ring16::BYTES <= kLogitRing && Ring8::BYTES <= kLogitRing &&
+                  Ring4::BYTES <= kLogitRing && Ring2::BYTES <= kLogitRing,
               "one ring size");
+// Grids of more than a block per CU (MANY).  With 96 KB one block runs on a CU
+// at a time; rings of 36 KB let two or three, and one block's decision run under
+// another's loads.  Route kernel, direct operand loads, 96 KB ring and these
+// (us): no look-ahead, 8 experts: d = 64, 16384 tokens 11.3, 20.2 and 12.6, 65536
+// 37.7, 70.1 and 30.4; d = 768, 32768 32.0, 42.8 and 28.5; d = 4096, 32768 86.5,
+// 95.7 and 81.8; 32 experts, d = 256, 32768 116, 84 and 84: with 17 experts or more
+// the large ring stays there.  Look-ahead, H = 2, 500 tokens: 8 experts, d = 64
+// 25.1, 40.3 and 26.4; 32, d = 768 68, 96 and 64; 256, d = 768 588, 893 and 568;
+// H = 3, 8 experts, d = 4096 275, 105 and 72.
+using RingMany = LogitRing<4, 48, 3>;    // one tile
+using RingMany4 = LogitRing<2, 96, 3>;   // up to four
+using RingMany7 = LogitRing<2, 144, 2>;  // seven at a time
+constexpr int kManyExperts = 7 * 16, kManyRing = RingMany::BYTES;
 
 // K splits of the logits (partial sums in LDS): wavefront w takes expert
 // column tile w % nct and every splits-th k-step of a slice
@@ -577,13 +584,12 @@ static __host__ __device__ inline int logit_splits(int E) {
   return nct < kRouteWaves ? kRouteWaves / nct : 1;
 }
 
-template <bool F32, int KS, bool MANY = false>
+template <bool F32, class R>
 __device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, char* ring, int base,
-                                             int nt) {
-  using R = LogitRing<KS, MANY>;
-  constexpr int ES = F32 ? 4 : 2;
+                                             int nt, int e0, int ne) {
+  constexpr int ES = F32 ? 4 : 2, KS = R::KSTEPS;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int E = p.E, nct = (E + 15) >> 4, splits = logit_splits(E);
+  const int E = p.E, nct = (ne + 15) >> 4, splits = logit_splits(E);
   const int hr = nt > 16 ? 32 : 16;          // token rows of a stage
   const int n_dma = (hr + 16 * nct) / R::RPI;
   const int rowb = p.d * ES;                 // bytes of a row, a multiple of 64
@@ -601,7 +607,7 @@ __device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, ch
     if (row < hr)
       src[i] = static_cast<const char*>(p.h) + (size_t)p.active_idx[base + min(row, nt - 1)] * rowb;
     else
-      src[i] = static_cast<const char*>(p.w_router) + (size_t)min(row - hr, E - 1) * rowb;
+      src[i] = static_cast<const char*>(p.w_router) + (size_t)(e0 + min(row - hr, ne - 1)) * rowb;
   }
   auto dma = [&](int g) {
     char* st = ring + (g % R::NST) * R::STAGE;
@@ -679,8 +685,8 @@ __device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, ch
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = 4 * hq + r;
-        if (e < E && row < nt) dz[row * E + e] = acc[t][0][r];
-        if (e < E && 16 + row < nt) dz[(16 + row) * E + e] = acc[t][1][r];
+        if (e < ne && row < nt) dz[row * E + e0 + e] = acc[t][0][r];
+        if (e < ne && 16 + row < nt) dz[(16 + row) * E + e0 + e] = acc[t][1][r];
       }
     }
   }
@@ -700,26 +706,28 @@ __device__ __forceinline__ void route_logits_any(const LayerParams& p, float* zs
                                                  int base, int nt) {
   const int nct = (p.E + 15) >> 4;
   if (nct == 1 && p.rb <= 16)
-    route_logits<F32, 16>(p, zs, ring, base, nt);
+    route_logits<F32, Ring16>(p, zs, ring, base, nt, 0, p.E);
   else if (nct == 1)
-    route_logits<F32, 8>(p, zs, ring, base, nt);
+    route_logits<F32, Ring8>(p, zs, ring, base, nt, 0, p.E);
   else if (nct <= 4)
-    route_logits<F32, 4>(p, zs, ring, base, nt);
+    route_logits<F32, Ring4>(p, zs, ring, base, nt, 0, p.E);
   else
-    route_logits<F32, 2>(p, zs, ring, base, nt);
+    route_logits<F32, Ring2>(p, zs, ring, base, nt, 0, p.E);
 }
 
-// One block = RB active tokens.  Phase 0: the layer's substitute table
-// (and, with look-ahead, the later layers' tables and transitions), one
-// wavefront per expert row.  Phase 1: router logits into LDS (MFMA 16x16x32
-// bf16 tiles, or fp32 FMA).  Phase 2: top-k and softmax weights with a lane
+// One block = p.rb active tokens.  Phase 0: the layer's substitute table, a
+// group of lanes per expert row.  Phase 1: router logits into LDS (16 x 16 MFMA
+// tiles in bf16 or fp32; FMAs for fp32 rows of partial steps), then, with
+// look-ahead, this and the later layers' candidate lists and transitions, a
+// wavefront per expert row.  Phase 2: top-k and softmax weights with a lane
 // group per token, then one thread per token runs the decision; with
 // look-ahead (LA) the block first evaluates the cost-to-go of every
 // candidate action of its tokens, one wavefront per token, its lanes over
 // (action, next-layer tuple) branches.  Phase 3: per-block expert histogram
 // for the bucketing.
 template <bool BF16, bool LA, bool MANY = false>
-__global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
+__global__ __launch_bounds__(64 * kRouteWaves, LA && MANY ? 4 : 1)  // (two blocks: 128 VGPRs)
+    void k_route(LayerParams p) {
   extern __shared__ __align__(16) float zs[];  // [logit_splits][RB][E] logits, K partial sums; LaLds
   __shared__ int s_cnt[TRIMMOE_MAX_EXPERTS];
   __shared__ int16_t s_subc[TRIMMOE_MAX_EXPERTS];  // best substitute (H = 1)
@@ -768,10 +776,20 @@ __global__ __launch_bounds__(64 * kRouteWaves) void k_route(LayerParams p) {
     if constexpr (LA) {
       char* ring = reinterpret_cast<char*>(zs + (size_t)logit_splits(E) * RB * E);
       static_assert(RB % 4 == 0, "the ring stays 16-byte aligned");
-      route_logits_any<!BF16>(p, zs, ring, base, nt);
+      if constexpr (MANY) {
+        if (E <= 16)
+          route_logits<!BF16, RingMany>(p, zs, ring, base, nt, 0, E);
+        else if (E <= 64)
+          route_logits<!BF16, RingMany4>(p, zs, ring, base, nt, 0, E);
+        else
+          for (int e0 = 0; e0 < E; e0 += kManyExperts)
+            route_logits<!BF16, RingMany7>(p, zs, ring, base, nt, e0, min(kManyExperts, E - e0));
+      } else {
+        route_logits_any<!BF16>(p, zs, ring, base, nt);
+      }
     } else if constexpr (MANY) {
       __shared__ __align__(16) char ring[kManyRing];
-      route_logits<!BF16, kManyKSteps, true>(p, zs, ring, base, nt);
+      route_logits<!BF16, RingMany>(p, zs, ring, base, nt, 0, E);
     } else {
       __shared__ __align__(16) char ring[kLogitRing];
       route_logits_any<!BF16>(p, zs, ring, base, nt);
@@ -1744,11 +1762,16 @@ hipError_t launch_route(const LayerParams& p, bool bf16, hipStream_t st) {
   const dim3 grid(nb), block(64 * kRouteWaves);
   if (p.horizon > 1) {
     // logits and tables, or before those the partial sums and their ring: the
-    // first is within route_lds_bytes, which validation limits, the second
-    // under 120 KB for any E
+    // first is within route_lds_bytes, which validation limits, the second at
+    // most 128 KB (256 experts: 32 KB of sums; fewer take 16 KB or less)
+    static_assert(kLogitRing + RB * TRIMMOE_MAX_EXPERTS * sizeof(float) <= kRouteLdsMax,
+                  "ring and partial sums within the limit of the tables");
     const size_t tables = zs + la_carve(nullptr, p.E, p.trans_b, p.k, p.horizon - 1, p.la_subs, nullptr);
-    const size_t lds = tables > parts + kLogitRing ? tables : parts + kLogitRing;
-    auto kern = bf16 ? k_route<true, true> : k_route<false, true>;
+    const bool many = bf16 && nb > p.n_cu;
+    const size_t ring = !many ? kLogitRing : p.E <= 16 ? RingMany::BYTES
+                        : p.E <= 64 ? RingMany4::BYTES : RingMany7::BYTES;
+    const size_t lds = tables > parts + ring ? tables : parts + ring;
+    auto kern = many ? k_route<true, true, true> : bf16 ? k_route<true, true> : k_route<false, true>;
     const hipError_t e = hipFuncSetAttribute(
         (const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

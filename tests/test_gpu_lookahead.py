@@ -83,6 +83,25 @@ def test_bf16_swiglu_top2_shared(H):
     assert stats["compared"] >= 0.8 * 512
 
 
+@pytest.mark.parametrize("E,k,d,H,T", [
+    (8, 1, 64, 3, 257),     # one expert column tile, one K slice
+    (16, 2, 832, 2, 600),   # ... a partial last slice; two tokens a block
+    (40, 2, 320, 2, 300),   # three column tiles
+    (112, 1, 192, 2, 300),  # seven, the most of one pass over the experts
+    # a second pass of one expert (top-1: of two slots over this many experts most decisions lie
+    # inside the bands, 264 of 300 tokens)
+    (113, 1, 192, 2, 300),
+    (256, 1, 64, 2, 300),   # three passes
+])
+def test_more_blocks_than_cus(E, k, d, H, T):
+    # grids of more than a block per CU: the small logit rings
+    cfg = workload("tiny_fp32", dtype="bf16", n_layers=3, n_experts=E, n_local=max(2, E // 4), top_k=k,
+                   normalize_topk=1, d_model=d, d_ff=64, n_tokens=T, vocab_exit=100, horizon=H,
+                   **RECIPE)
+    _, _, _, stats = _stack(cfg, 1e-3, 1e-4)
+    assert stats["compared"] >= 0.5 * T
+
+
 def test_top4_sixty_experts_two_entry_rows():
     # Qwen-like routing: 60 experts top-4 (one candidate per remote slot: 17
     # candidate actions, 16 tuples per level with 2-entry rows), horizon 2
