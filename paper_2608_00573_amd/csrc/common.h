@@ -87,6 +87,22 @@ inline bool big_exit(bool bf16, int T, int V, int d) {
 }
 // batches of this many tokens or more use the 256-token exit-head tile
 constexpr int kWideTokens = 4096;
+// ... and output heads over n_rows rows where its tiles come in no more rounds
+// of the grid than they are worth: a 256 x 256 tile takes nearly twice as long as
+// a 256 x 128 one, so against one round of those, or three against its two, it
+// loses (argmax kernel in 256 x 128 tiles and on the large-group core, d = 2048,
+// us: V = 4000, 1500 rows, 192 tiles against 96: 35 and 62; V = 6000, 1500 rows, 288
+// against 144: 66 and 61; 3000 rows, 576 against 288: 102 and 121; V = 16000, 2048
+// rows, 1008 against 504: 146 and 116).  From kWideTokens rows the other tile is
+// 256 x 256 too, and better at short K and few vocabulary tiles (d = 2048, 6000
+// rows: V = 6000 176 and 186, V = 8000 190 and 180; d = 4096, V = 6000: 317 and 299)
+inline bool big_argmax(int n_rows, int V, int d, int n_cu) {
+  if (!big_exit(true, n_rows, V, d)) return false;
+  const int vt = (V + kBigBM - 1) / kBigBM;
+  if (n_rows >= kWideTokens) return d >= 2 * kBigExitDModel || vt >= 32;
+  const int tiles = vt * ((n_rows + 127) / 128), big_tiles = vt * ((n_rows + 255) / 256);
+  return tiles > 3 * n_cu || (tiles > n_cu && big_tiles <= n_cu);
+}
 constexpr int kGemmBN = 128;
 constexpr int kGemmBK = 64;
 // K splits of the routed down GEMM (128-row tiles), from the live tile and row

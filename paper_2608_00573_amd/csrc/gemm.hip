@@ -2074,9 +2074,9 @@ hipError_t launch_head_argmax_partials(bool bf16, const void* W, const float* bi
     ExitArgs a{static_cast<const bf16_t*>(W), static_cast<const bf16_t*>(H), bias, n_rows_dev, V,
                K, n_vtiles, partials};
     if (exit_streams(true, true, n_rows, V, K)) return launch_exit_skinny(a, true, st);
-    // wide models and large batches on the large-group core, as the exit head
-    // (V = 151936, d = 2048, 2048 rows: 1365 -> 1005 us)
-    if (big_exit(true, n_rows, V, K)) {
+    // (V = 151936, d = 2048, 2048 rows in 256 x 128 tiles 1365 us, on the
+    // large-group core 1005)
+    if (big_argmax(n_rows, V, K, n_cu)) {
       const dim3 grid(min(n_vtiles * cdiv(n_rows, big::BN), n_cu));
       hipLaunchKernelGGL(k_argmax_big, grid, dim3(big::THREADS), 0, st, a);
     } else if (n_rows <= kSkinnyTokens) {

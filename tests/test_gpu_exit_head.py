@@ -37,7 +37,9 @@ def _mat(seed, tid, shape, sigma, dtype):
     (torch.bfloat16, 24600, 2112, 40),    # ... from 33 rows on with many vocabulary rows
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles, ragged vocabulary
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
-    (torch.bfloat16, 700, 2048, 1030),    # large-group tiles, ragged rows and vocabulary
+    (torch.bfloat16, 700, 2048, 1030),    # ... too few for large-group tiles
+    (torch.bfloat16, 7900, 2048, 1030),   # large-group tiles, ragged rows and vocabulary
+    (torch.bfloat16, 300, 4096, 4100),    # ... wide rows, one partial vocabulary tile
 ])
 def test_head_argmax_matches_oracle(dtype, V, d, Q):
     log(f"[exit-head] argmax {dtype} V={V} d={d} Q={Q}")
@@ -59,7 +61,7 @@ def test_head_argmax_matches_oracle(dtype, V, d, Q):
     (torch.bfloat16, 1003, 2112, 15),     # ... long K
     (torch.bfloat16, 5000, 128, 700),     # 256 x 128 tiles
     (torch.bfloat16, 3000, 64, 4100),     # 256 x 256 tiles
-    (torch.bfloat16, 700, 2048, 1030),    # large-group tiles
+    (torch.bfloat16, 7900, 2048, 1030),   # large-group tiles
 ])
 def test_head_argmax_without_a_largest_logit(dtype, V, d, Q):
     # NaN never wins, and where no logit is above -inf the answer is row 0
