@@ -560,7 +560,9 @@ size_t train_ws_min(int n_rows) {
 }
 // blocks of the one-pass step: a row per wavefront (4 a block) until every CU
 // has a block; more blocks would only add partials to write and read back
-int train_blocks(int n_rows) { return std::min(kTrainBlocks, cdiv(std::max(n_rows, 1), 4)); }
+int train_blocks(int n_rows) {
+  return n_rows >= 4 * kTrainBlocks ? kTrainBlocks : cdiv(std::max(n_rows, 1), 4);
+}
 size_t train_ws_rows(int nb, int slots) {
   return align256((size_t)nb * sizeof(double2)) + align256((size_t)nb * slots * sizeof(double));
 }

@@ -181,11 +181,13 @@ __global__ __launch_bounds__(64 * kBceWaves) void k_bce_rows(const T* H, const u
   __shared__ double s_col[kBceWaves][SLOTS];
   __shared__ double2 s_rl[kBceWaves];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int q0 = blockIdx.x * kBceWaves + wave, step = gridDim.x * kBceWaves;
+  // (unsigned: the row after the last one passes 2^31 - 1 in the largest batches)
+  const unsigned q0 = blockIdx.x * kBceWaves + wave, step = gridDim.x * kBceWaves;
+  const unsigned rows = n_rows;
   struct alignas(sizeof(T) * V) Vec {
     T e[V];
   };
-  auto load_row = [&](Vec(&x)[NC], int q) {
+  auto load_row = [&](Vec(&x)[NC], unsigned q) {
     const T* h = H + (size_t)q * d;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -197,7 +199,7 @@ __global__ __launch_bounds__(64 * kBceWaves) void k_bce_rows(const T* H, const u
     }
   };
   Vec x[NC], xn[NC];
-  load_row(x, min(q0, n_rows - 1));
+  load_row(x, min(q0, rows - 1));
   float wv[NC][V];
 #pragma unroll
   for (int i = 0; i < NC; ++i)
@@ -213,9 +215,9 @@ __global__ __launch_bounds__(64 * kBceWaves) void k_bce_rows(const T* H, const u
 #pragma unroll
     for (int u = 0; u < V; ++u) g[i][u] = 0.0;
   double sr = 0.0, sl = 0.0;
-  for (int q = q0; q < n_rows; q += step) {
+  for (unsigned q = q0; q < rows; q += step) {
     const float label = y[q] ? 1.f : 0.f;
-    load_row(xn, min(q + step, n_rows - 1));
+    load_row(xn, min(q + step, rows - 1));
     float acc = 0.f;
 #pragma unroll
     for (int i = 0; i < NC; ++i)

@@ -309,6 +309,18 @@ def test_static_entry_validates_before_any_device_call():
                                           None) == -1
 
 
+@pytest.mark.parametrize("rows", [0, 1, 1023, 1024, 5000, 2**31 - 1])
+def test_training_workspace_holds_either_step(rows):
+    # residuals (4 bytes) and losses (8) of every row, or 256 blocks' partial
+    # sums: 16 bytes and 4096 fp64 columns each (fewer blocks for fewer rows)
+    n = C.c_size_t(0)
+    assert abi.lib().trimmoe_train_exit_head_workspace_size(rows, C.byref(n)) == abi.TRIMMOE_OK
+    pad = lambda b: (b + 255) // 256 * 256
+    r = max(rows, 1)
+    blocks = min(256, (r + 3) // 4)
+    assert n.value == max(pad(4 * r) + pad(8 * r), pad(16 * blocks) + pad(8 * 4096 * blocks))
+
+
 def test_empty_batch_is_a_no_op_without_device_calls():
     # a batch of no tokens: every entry point that runs the path validates
     # its arguments and returns TRIMMOE_OK before any device call, writing

@@ -165,6 +165,26 @@ def test_training_steps_at_the_edges(dtype, Q, d):
         assert np.allclose(loss.cpu().numpy(), lw, rtol=1e-5, atol=1e-5)
 
 
+def test_training_step_of_the_most_rows():
+    """2^31 - 1 rows of one zero each: the row index of the one-pass step runs
+    past the largest int.  Every row adds the same residual sigmoid(c) and
+    loss log(1 + e^c); fp64 sums of n equal terms are within n * 2^-53."""
+    Q = 2**31 - 1
+    log(f"[exit-head] {Q} rows")
+    H = torch.zeros(Q, 1, dtype=torch.float32, device=DEV)
+    y = torch.zeros(Q, dtype=torch.uint8, device=DEV)
+    w = torch.zeros(1, dtype=torch.float32, device=DEV)
+    c = torch.full((1,), 0.5, dtype=torch.float32, device=DEV)
+    loss = torch.zeros(1, dtype=torch.float32, device=DEV)
+    abi.trimmoe_train_exit_head(H, y, 1, 1.0, w, c, loss)
+    torch.cuda.synchronize()
+    assert w.item() == 0.0
+    assert c.item() == pytest.approx(0.5 - 1.0 / (1.0 + np.exp(-0.5)), abs=1e-6)
+    assert loss.item() == pytest.approx(np.log1p(np.exp(0.5)), rel=1e-6)
+    del H, y
+    torch.cuda.empty_cache()
+
+
 def test_trained_heads_drive_a_sigmoid_stack():
     # no planted exit direction and wider experts, so that some tokens'
     # predictions still change after layer 0 (labels of both kinds)
