@@ -130,26 +130,43 @@ def host_cpu():
 
 def class_kernel(cls, cfg):
     """The library kernel(s) of a kernel class at the workload's batch size,
-    by the library's tile selection: grouped GEMMs with at least 1024 rows
-    per expert on average and the shared expert from 4096 tokens run the
-    256 x 256 large-group core, the exit head of models with d >= 2048 from
-    1024 tokens too; everything else the 8-wavefront streaming core."""
+    by the library's tile selection (bf16; fp32 models run the 8-wavefront
+    core): the weight-streaming kernels take the grouped GEMMs up to 64 tokens,
+    the shared expert up to 128, and the exit head of up to 64 tokens where
+    rows are long (d >= 2048) and, beyond 16 tokens, many (V >= 24576), or W
+    exceeds 256 MB; the 256 x 256 large-group core takes grouped GEMMs with at
+    least 1024 rows per expert on average, the shared expert from 4096 tokens
+    and the exit head of models with d >= 2048 from 1024 tokens; everything
+    else the 8-wavefront core."""
     T, k, E, d = cfg["n_tokens"], cfg["top_k"], cfg["n_experts"], cfg["d_model"]
+    V = cfg["vocab_exit"]
     bf16 = cfg["dtype"] == "bf16"
     swiglu = cfg["act"] == "swiglu"
     big = bf16 and T * k >= 1024 * E
+    skinny = bf16 and T <= 64
     if cls == "up":
-        name = ("k_ffn_big<0>" if swiglu else "k_ffn_big<1>") if big else \
+        name = "k_ffn_skinny<up>" if skinny else \
+            ("k_ffn_big<0>" if swiglu else "k_ffn_big<1>") if big else \
             ("k_ffn_mma<128x128 dual, up>" if swiglu else "k_ffn_mma<128x256, up>")
         return name + " (grouped up/gate + activation)"
     if cls == "down":
-        return ("k_ffn_big<2>" if big else "k_ffn_mma<128x256, down>") + " (grouped down)"
+        name = "k_ffn_skinny<down>" if skinny else "k_ffn_big<2>" if big else "k_ffn_mma<128x256, down>"
+        return name + " (grouped down)"
     if cls == "exit":
-        return ("k_exit_big" if bf16 and T >= 1024 and d >= 2048 else "k_exit_mma") + \
+        wide, huge = d >= 2048, V * d >= 1 << 27
+        if T <= 16:
+            streams = V <= 16 or wide or huge
+        elif V <= 16:
+            streams = T <= 32 or wide
+        else:
+            streams = (wide and V >= 24576) or (huge and T > 32)
+        return ("k_exit_skinny" if skinny and streams else
+                "k_exit_big" if bf16 and T >= 1024 and d >= 2048 else "k_exit_mma") + \
             " (exit head + softmax partials)"
     return {"route": "k_route (route, substitution, skip)",
             "bucket": "k_scan + k_bucket (bucketing)",
-            "shared": "k_ffn_mma / k_ffn_big (shared expert)",
+            "shared": ("k_ffn_skinny" if bf16 and T <= 128 else "k_ffn_big" if bf16 and T >= 4096 else
+                       "k_ffn_mma + k_ffn_dense_down" if bf16 else "k_ffn_mma") + " (shared expert)",
             "combine": "k_combine (weighted combine)",
             "gate": "k_exit_reduce + k_compact (exit gate)"}[cls]
 

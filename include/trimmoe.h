@@ -467,8 +467,13 @@ int trimmoe_consistency_labels(int32_t n_rows, const int32_t* pred, const int32_
  * each epoch starts from.  h [n_rows, d] in `dtype` (bf16: d a multiple of
  * 64).  Sums run in a fixed order in fp64: repeated runs give identical
  * weights.  Needs a 256-byte aligned workspace of
- * trimmoe_train_exit_head_workspace_size(n_rows) bytes (room for partial
- * column sums, with which the rows are read once per step).
+ * trimmoe_train_exit_head_workspace_size(n_rows) bytes: room for the partial
+ * column sums of a head of up to 4096 columns, with which a step reads the
+ * rows once.  A workspace of 4 and 8 bytes per row, each rounded up to 256, is
+ * accepted too and, like wider heads, takes steps that read the rows twice.
+ * The two kinds of step add in different orders, as do rows that start on a
+ * 16-byte boundary and rows that do not: weights are identical between runs
+ * that agree in both, and differ in rounding (fp32 logits) otherwise.
  */
 int trimmoe_train_exit_head_workspace_size(int32_t n_rows, size_t* bytes);
 int trimmoe_train_exit_head(int32_t dtype, int32_t d_model, int32_t n_rows, const void* h,

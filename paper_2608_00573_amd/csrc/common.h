@@ -12,8 +12,8 @@ namespace trimmoe {
 typedef uint16_t bf16_t;
 
 // ---------------------------------------------------------------- tiling --
-// tokens handled by one block of the route and permute kernels (at most;
-// with look-ahead a small batch uses fewer per block: route_block_tokens)
+// tokens handled by one block of the route and permute kernels (at most; small
+// batches use fewer per block: route_block_tokens)
 constexpr int kRouteTokens = 32;
 // route blocks the look-ahead aims for: one per CU
 constexpr int kLookaheadBlocks = 256;

@@ -1,6 +1,7 @@
-// Weight-streaming GEMMs for decode-sized batches (bf16, up to
-// kSkinnyTokens tokens): grouped up/gate and down projections, the shared
-// expert and the exit head.
+// Weight-streaming GEMMs for decode-sized batches (bf16): grouped up/gate and
+// down projections of up to kSkinnyTokens tokens, the shared expert of up to
+// kSkinnyDenseTokens, and exit heads of up to kSkinnyTokens tokens where they
+// beat the 128 x 32 tiles (exit_streams).
 //
 // With a few rows per expert every weight is used once per row tile, so the
 // kernels are bound by reading W from HBM, and by the texture path that
@@ -33,7 +34,8 @@
 // the weights' traffic.  A plain read kernel reaches 6.2-6.6 TB/s.  Qwen shapes,
 // 16 tokens: up 54 -> 42, down 29 -> 27, shared expert 104 -> 27, exit 125 -> 97.
 // Above kSkinnyTokens the activations would outweigh the weights further and
-// the matrix cores no longer wait for them: the 128-row tiles take over.
+// the matrix cores no longer wait for them: the 128-row tiles take over (the
+// shared expert's weights stay in the last-level cache for a second pass).
 #include <math.h>
 
 #include "gemm.h"

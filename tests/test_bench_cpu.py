@@ -64,4 +64,12 @@ def test_kernel_names_follow_the_tile_selection():
     assert bench.class_kernel("down", workload("mixtral_8x7b_prefill")).startswith("k_ffn_big<2>")
     assert bench.class_kernel("exit", workload("qwen_moe_a2_7b")).startswith("k_exit_big")
     assert bench.class_kernel("exit", workload("switch_base_8e")).startswith("k_exit_mma")
-    assert bench.class_kernel("up", workload("mixtral_8x7b_decode")).startswith("k_ffn_mma")
+    # decode-sized batches stream the weights
+    decode = workload("mixtral_8x7b_decode")
+    assert bench.class_kernel("up", decode).startswith("k_ffn_skinny")
+    assert bench.class_kernel("down", decode).startswith("k_ffn_skinny")
+    assert bench.class_kernel("exit", decode).startswith("k_exit_skinny")
+    assert bench.class_kernel("exit", workload("switch_base_8e", n_tokens=64)).startswith("k_exit_mma")
+    assert bench.class_kernel("up", workload("switch_base_8e")).startswith("k_ffn_mma")
+    assert bench.class_kernel("up", workload("tiny_fp32")).startswith("k_ffn_mma")
+    assert bench.class_kernel("shared", workload("qwen_moe_a2_7b", n_tokens=100)).startswith("k_ffn_skinny")

@@ -226,8 +226,9 @@ def test_lds_reads_land_before_their_registers_are_used(asm, kernel):
 def _first_core(asm):
     # every instance of the first core's kernels (inline-asm fragment reads
     # with explicit waits, MFMAs by builtin)
-    names = re.findall(r"^(_ZN7trimmoe\w*k_(?:ffn|exit)_mma\w*):", asm, re.M)
-    assert names
+    names = re.findall(r"^(_ZN7trimmoe\w*k_(?:ffn_mma|exit_mma|ffn_dense_down)\w*):", asm, re.M)
+    for kernel in ("k_ffn_mma", "k_exit_mma", "k_ffn_dense_down"):
+        assert any(kernel in n for n in names), kernel
     return names
 
 
@@ -364,6 +365,19 @@ def test_race_checker_finds_planted_races():
             "s_load_dword s0, s[2:3], 0x0", "s_waitcnt lgkmcnt(1)", "v_mov_b32 v10, v1",
             "s_endpgm"]
     assert _lds_races(smem)
+
+
+def test_lds_store_checker_finds_planted_hazards():
+    # a store of an MFMA's result right after it, after too few wait states and after enough
+    mfma = "v_mfma_f32_16x16x32_bf16 v[0:3], v[8:11], v[12:15], v[0:3]"
+    assert _mfma_lds_hazards([mfma, "ds_write_b128 v16, v[0:3]", "s_endpgm"])
+    assert _mfma_lds_hazards([mfma, "s_nop 7", "s_nop 7", "ds_write_b128 v16, v[0:3]", "s_endpgm"])
+    assert not _mfma_lds_hazards([mfma, "s_nop 7", "s_nop 7", "s_nop 7", "ds_write_b128 v16, v[0:3]",
+                                  "s_endpgm"])
+    # a store of other registers, and one reached through a branch
+    assert not _mfma_lds_hazards([mfma, "ds_write_b128 v16, v[4:7]", "s_endpgm"])
+    assert _mfma_lds_hazards([mfma, "s_branch .LBB0_2", ".LBB0_1:", "s_endpgm", ".LBB0_2:",
+                              "ds_write_b128 v16, v[0:3]", "s_branch .LBB0_1"])
 
 
 def test_checker_finds_a_planted_hazard():

@@ -165,6 +165,42 @@ def test_training_steps_at_the_edges(dtype, Q, d):
         assert np.allclose(loss.cpu().numpy(), lw, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("dtype,Q,d", [
+    (torch.bfloat16, 70, 64), (torch.bfloat16, 301, 576), (torch.bfloat16, 9, 4096),
+    (torch.float32, 301, 260), (torch.float32, 9, 4096),
+])
+def test_training_of_unaligned_hidden_states(dtype, Q, d):
+    """Hidden states one element past a 16-byte boundary: element-wide loads
+    whatever d, in both forms of the step (bounds as for the aligned ones)."""
+    log(f"[exit-head] unaligned {dtype} Q={Q} d={d}")
+    epochs, lr = 3, 0.5
+    H, Hn = _mat(41, 6, (Q, d), 1.0, dtype)
+    y = (np.arange(Q) % 3 == 0).astype(np.uint8)
+    buf = torch.empty(1 + H.numel(), dtype=dtype, device=DEV)
+    Hd = buf[1:].view(H.shape)
+    Hd.copy_(H)
+    assert Hd.data_ptr() % 16 != 0
+    yd = torch.from_numpy(y).to(DEV)
+    ww, cw, lw = X.train_exit_head(Hn, y, epochs, lr)
+    small = ((Q * 4 + 255) // 256 + (Q * 8 + 255) // 256) * 256
+    for nbytes in (None, small):
+        w = torch.zeros(d, dtype=torch.float32, device=DEV)
+        c = torch.zeros(1, dtype=torch.float32, device=DEV)
+        loss = torch.zeros(epochs, dtype=torch.float32, device=DEV)
+        if nbytes is None:
+            abi.trimmoe_train_exit_head(Hd, yd, epochs, lr, w, c, loss)
+        else:
+            ws = abi._aligned_ws(nbytes, Hd.device)
+            rc = abi.lib().trimmoe_train_exit_head(
+                abi._dtype_code(Hd), d, Q, abi._ptr(Hd), abi._ptr(yd), epochs, lr, abi._ptr(w),
+                abi._ptr(c), abi._ptr(loss), abi._ptr(ws), nbytes, abi._stream_handle(None))
+            assert rc == abi.TRIMMOE_OK
+        torch.cuda.synchronize()
+        assert np.allclose(w.cpu().numpy(), ww, rtol=1e-4, atol=1e-5)
+        assert c.item() == pytest.approx(cw, rel=1e-4, abs=1e-5)
+        assert np.allclose(loss.cpu().numpy(), lw, rtol=1e-5, atol=1e-5)
+
+
 def test_training_step_of_the_most_rows():
     """2^31 - 1 rows of one zero each: the row index of the one-pass step runs
     past the largest int.  Every row adds the same residual sigmoid(c) and
