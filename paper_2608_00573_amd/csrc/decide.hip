@@ -620,7 +620,7 @@ __device__ __forceinline__ void route_logits(const LayerParams& p, float* zs, ch
     }
   };
   const int fr = lane & 15, hq = lane >> 4;
-  const uint32_t ring0 = (uint32_t)(uintptr_t)(const lds_byte*)ring;
+  const uint32_t ring0 = lds_addr(ring);
   f32x4_t acc[2][2] = {};  // [expert tile of this wavefront][token tile]
   const int kq = wave / nct;
   const bool busy = nct >= kRouteWaves || kq < splits;

@@ -13,8 +13,13 @@ static inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 typedef __attribute__((address_space(3))) char lds_byte;
 
-// 16-byte chunk c of row r sits at chunk c ^ swz16(r) of its LDS row, so that
-// the 16 rows of a fragment read spread over the banks
+__device__ __forceinline__ uint32_t lds_addr(const char* p) {
+  return (uint32_t)(uintptr_t)(const lds_byte*)(p);
+}
+
+// 16-byte chunk c of row r sits at chunk c ^ swz16(r) of its LDS row: 8
+// consecutive rows, or 16 consecutive rows split by parity, then touch distinct
+// bank groups
 __device__ __forceinline__ int swz16(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 // barrier for plain LDS traffic that leaves vector-memory operations in flight

@@ -60,10 +60,6 @@ struct Tile {
   static_assert(BM % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0, "load passes");
 };
 
-// 16-byte chunk c of row r sits at chunk c ^ swz(r): 8 consecutive rows, or
-// 16 consecutive rows split by parity, then touch distinct bank groups.
-__device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
-
 // accumulator element -> tile-local (row, col)
 template <class T>
 __device__ __forceinline__ int acc_row(int wm, int i, int r, int lane) {
@@ -81,7 +77,7 @@ __device__ __forceinline__ int acc_col(int wn, int j, int lane) {
 // operand path spends most of its non-MFMA issue time on).  Three LDS stages
 // form a ring: slice g+2 is in flight while slice g is computed and slice
 // g+1 has landed.  Lane l of the DMA that covers tile rows r..r+7 loads row
-// r + l/8, chunk (l % 8) ^ swz(row), so the LDS image is the same swizzled
+// r + l/8, chunk (l % 8) ^ swz16(row), so the LDS image is the same swizzled
 // layout the fragment reads expect.
 //
 // Waits are explicit.  The compiler cannot tell that a DMA into one stage
@@ -96,15 +92,9 @@ __device__ __forceinline__ int acc_col(int wn, int j, int lane) {
 //     waves, so the next stage may be read and the oldest one rewritten.
 // Only LDS DMAs and rare stores are outstanding vector-memory operations in
 // these loops; extra newer operations only make a vmcnt wait stricter.
-typedef __attribute__((address_space(3))) char lds_char;
-
 __device__ __forceinline__ void dma16(const bf16_t* g, char* l) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g),
-                                   (lds_char*)(l), 16, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t lds_addr(const char* p) {
-  return (uint32_t)(uintptr_t)(const lds_char*)(p);
+                                   (lds_byte*)(l), 16, 0, 0);
 }
 
 __device__ __forceinline__ bf16x8_t lds_read(uint32_t a) {
@@ -167,7 +157,7 @@ struct DPtrs {
 __device__ __forceinline__ int dma_row(int i, int rows_per_pass) {
   return ((int)threadIdx.x >> 3) + rows_per_pass * i;
 }
-__device__ __forceinline__ int dma_col(int row) { return 8 * (((int)threadIdx.x & 7) ^ swz(row)); }
+__device__ __forceinline__ int dma_col(int row) { return 8 * (((int)threadIdx.x & 7) ^ swz16(row)); }
 
 // A rows a_src[i] (matrix rows, already clamped) of A; B rows b_row0 + r,
 // r clamped to b_valid - 1, of B0 (and B1); K columns from k_begin
@@ -211,7 +201,7 @@ struct FragAddr {
     a = (wm * T::WM + fr) * 128;
     b = T::A_BYTES + (wn * T::WN + fr) * 128;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) ch[ks] = ((2 * ks + hi) ^ swz(fr)) << 4;
+    for (int ks = 0; ks < 4; ++ks) ch[ks] = ((2 * ks + hi) ^ swz16(fr)) << 4;
   }
   __device__ __forceinline__ void read(Frags<T>& f, uint32_t stage, int ks) const {
     const uint32_t pa = stage + a + ch[ks], pb = stage + b + ch[ks];
@@ -845,7 +835,7 @@ __device__ __forceinline__ void big_dma(uint32_t bst, int wave, const BigRows& q
                                         int u) {
   const __amdgpu_buffer_rsrc_t& rs = DUAL && u >= 4 ? b.rb1 : b.rb0;
   const uint32_t dst = bst + (uint32_t)((8 * wave + big::RPP * u) * big::RB);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_char*)(uintptr_t)dst, 16, q.off[8 + u], b.ko, 0,
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_byte*)(uintptr_t)dst, 16, q.off[8 + u], b.ko, 0,
                                            0);
 }
 
@@ -853,7 +843,7 @@ __device__ __forceinline__ void big_dma(uint32_t bst, int wave, const BigRows& q
 __device__ __forceinline__ void big_dma_a(uint32_t ast, int wave, const BigRows& q, const BigSrc& b,
                                           int u) {
   const uint32_t dst = ast + (uint32_t)((8 * wave + big::RPP * u) * big::RB);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(b.ra, (lds_char*)(uintptr_t)dst, 16, q.off[u], b.ko, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(b.ra, (lds_byte*)(uintptr_t)dst, 16, q.off[u], b.ko, 0, 0);
 }
 
 // MFMA slot T of a k-step (LAST: the second of the slice) from fragments fa,
@@ -1157,7 +1147,7 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
   uint32_t a_lane[2], b_lane[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const uint32_t ch = ((4 * ks + hk) ^ swz(fr)) << 4;
+    const uint32_t ch = ((4 * ks + hk) ^ swz16(fr)) << 4;
     a_lane[ks] = (wm * 128 + fr) * big::RB + ch;
     b_lane[ks] = ((DUAL ? wn * 64 : wn * 128) + fr) * big::RB + ch;
   }
@@ -1165,7 +1155,7 @@ __global__ __launch_bounds__(big::THREADS) void k_ffn_big(FfnArgs a) {
   // of each row segment and writes it to chunk slot tid & 7 of the LDS row,
   // so the stage holds the swizzled layout the fragment reads expect
   const int r0 = tid >> 3;
-  const int cc = 8 * ((tid & 7) ^ swz(r0));
+  const int cc = 8 * ((tid & 7) ^ swz16(r0));
   const __amdgpu_buffer_rsrc_t ra = buf_rsrc(a.X);
   AccBig acc;
   // output tile (mt, nt) over K slices [ka, ka + nkp) into its rows, or
@@ -1722,12 +1712,12 @@ __device__ __forceinline__ void exit_big(const ExitArgs& a, char* lds) {
   uint32_t a_lane[2], b_lane[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const uint32_t ch = ((4 * ks + hk) ^ swz(fr)) << 4;
+    const uint32_t ch = ((4 * ks + hk) ^ swz16(fr)) << 4;
     a_lane[ks] = (wm * 128 + fr) * big::RB + ch;
     b_lane[ks] = (wn * 128 + fr) * big::RB + ch;
   }
   const int r0 = tid >> 3;
-  const int cc = 8 * ((tid & 7) ^ swz(r0));
+  const int cc = 8 * ((tid & 7) ^ swz16(r0));
   BigRows q;
   q.ra = buf_rsrc(a.W);
   q.none = buf_rsrc_empty(a.W);

@@ -52,10 +52,6 @@ constexpr int LDS = RING + RED;
 constexpr int KSTEP = 32;                        // K of one MFMA
 }  // namespace skinny
 
-__device__ __forceinline__ uint32_t lds_offset(const char* p) {
-  return (uint32_t)(uintptr_t)(const lds_byte*)(p);
-}
-
 // LDS reads and writes of the sums and fragments are asm: the compiler cannot
 // tell that they never alias a DMA in flight and would wait for all of them.
 // Every read waits for its own data in the same statement.
@@ -169,7 +165,7 @@ __device__ __forceinline__ void skinny_stream(char* lds, const XSrc<T::MT>& xs, 
     for (int u = 0; u < units; ++u) epi(u, acc);
     return;
   }
-  const uint32_t ring = lds_offset(lds) + wave * 2 * T::SET;
+  const uint32_t ring = lds_addr(lds) + wave * 2 * T::SET;
   // DMA lanes: LPR lanes run along a row of the set, RPI rows per operation
   constexpr int LPR = 4 * U, RPI = 64 / LPR;
   const uint32_t rowb = (uint32_t)ks * (skinny::KSTEP * 2);
@@ -309,7 +305,7 @@ __device__ __forceinline__ bool skinny_sum(char* lds, int& par,
   constexpr int NB = T::NB, MT = T::MT, GR = T::GR;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t red =
-      lds_offset(lds) + skinny::RING + lane * 16 + (T::PAR ? par * skinny::WAVES * T::PART : 0);
+      lds_addr(lds) + skinny::RING + lane * 16 + (T::PAR ? par * skinny::WAVES * T::PART : 0);
   par ^= 1;
   // the compiler does not see that the asm stores read the results of MFMAs
   // (19 wait states at most for these)
